@@ -836,7 +836,7 @@ def main():
     else:                           # CSR sweep reads the SpMV bytes, and 8 N more for the lagged step
         layout_bytes = bytes_per_launch + 8 * N
         layout_formula = "28 N + 8 E"
-        kernel = ("k_pr_iter_binned<true>" if info["row_mapping"] == -2
+        kernel = ("k_pr_iter_panels" if info["row_mapping"] == -2
                   else f"k_pr_iter_csr<{info['row_mapping']}, true>")
     achieved = bytes_per_launch / avg_launch_s / 1e9
     traffic_rec = traffic_record(TRAFFIC_FILE, kernel)

@@ -830,6 +830,7 @@ fl_status prepare_pr(fl_ctx *ctx, fl_plan *p, const Resolved &r, int lanes, PrAr
         if (bst != FL_OK) return bst;
         a.bin_rows = p->bin_rows;
         a.bins = p->bins;
+        a.lag = r.lag ? 1 : 0;   // its own kernel and workgroup size
     }
     a.adjacent = p->adjacent;
     a.x_bytes = kind == fl::kSweepSlots ? x_bytes_of(p) : 0;
@@ -840,8 +841,9 @@ fl_status prepare_pr(fl_ctx *ctx, fl_plan *p, const Resolved &r, int lanes, PrAr
     const int64_t resident =
         std::max<int64_t>(fl::kXcds, (int64_t)std::max(per_cu, 1) * ctx->num_cus / fl::kXcds * fl::kXcds);
     const int64_t rows_per_wg = kind == fl::kSweepSlots ? fl::kBlock : (kind == fl::kSweepBinned ? 1 : fl::kBlock / lanes);
-    const int64_t groups = kind == fl::kSweepBinned ? std::max<int64_t>(p->bins.tiles, 1)
-                                                    : (p->n + rows_per_wg - 1) / rows_per_wg;
+    const int64_t groups = kind == fl::kSweepBinned
+                               ? std::max<int64_t>(r.lag ? fl::bin_panels(p->bins) : p->bins.tiles, 1)
+                               : (p->n + rows_per_wg - 1) / rows_per_wg;
     grid = (int)std::min<int64_t>(resident, (groups + fl::kXcds - 1) / fl::kXcds * fl::kXcds);
     fl_status st = ensure_pr_buffers(ctx, p, kind == fl::kSweepSlots, r.lag);
     if (st != FL_OK) return st;

@@ -22,6 +22,7 @@ constexpr int kXcds = 8;                          // MI355X: 8 XCDs, workgroups 
 constexpr int kBatch = 16;                        // candidate slots whose loads are issued together
 constexpr int kMaxFinishGrid = 1024;              // workgroups of the batched step kernel (grid-stride)
 constexpr int kFinishBlock = 1024;                // threads of a step kernel workgroup (1 mod 3)
+constexpr int kPanelBlock = 512;                  // threads of a workgroup of the lagged binned sweep (8 waves)
 constexpr int kFillStage = 6144;                  // col_idx entries of a tile assembled in LDS by the fill
 constexpr int kSmallTiles = 16;                   // batch members of at most this many tiles iterate in one workgroup
 
@@ -283,6 +284,8 @@ hipError_t launch_bin_rows(const int32_t *row_ptr, int32_t n, const int8_t *clas
 // class at a time this way), without the step kernel.
 hipError_t launch_pr_sweep_binned(const PrArgs &a, const BinTable &t, int grid, hipStream_t stream);
 hipError_t pr_binned_blocks_per_cu(int *blocks, bool lag = false);
+// Panels (one workgroup at a time each) of a lagged binned sweep.
+int32_t bin_panels(const BinTable &t);
 hipError_t launch_batch_sweep_binned(const BatchMember *members, const TileRef *tiles, const int32_t *range_dev,
                                      int grid, hipStream_t stream);
 hipError_t batch_sweep_binned_blocks_per_cu(int *blocks);

@@ -54,6 +54,12 @@ __device__ __forceinline__ T wave_sum(T x) {
     return x;
 }
 
+// The value of another lane, as a DPP operand (CTRL: the DPP control).
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+
 __device__ __forceinline__ float wave_min(float x) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) x = fminf(x, __shfl_xor(x, o, 64));
@@ -139,6 +145,13 @@ __device__ T scan_tiles(const T *in, T *out, int n_tiles) {
         carry += tot;
     }
     return carry;
+}
+
+// Orders a wave's LDS stores before its later LDS loads by other lanes (no
+// barrier: the lanes of a wave run together and LDS serves a wave in order).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 // ---------------------------------------------------------------------------
@@ -888,7 +901,15 @@ __global__ __launch_bounds__(kBlock) void k_seg_fill(const SegBuild *__restrict_
                        g->minima);
 }
 
-// Generic version for spaces with more than kMaxSlots candidate slots.
+// Generic version for spaces with more than kMaxSlots candidate slots: one
+// node per lane, the candidates of a parameter in batches of kGenericBatch.
+// A batch loads the fitness of its candidates together, then the node ids of
+// those that are worse; the lanes' hits go through LDS, and the wave writes
+// four rows' hits per store, each a contiguous piece of its row.  (One
+// 4-byte store per edge, every lane to its own row, touches a line per lane:
+// with candidates taken one by one that form ran 272 us at radices
+// 64,56,40,3, 26 M edges over 350 k nodes, this one 97 us.)
+constexpr int kGenericBatch = 16;
 template <bool ADJ>
 __global__ __launch_bounds__(kBlock) void k_fill_generic(SpaceDesc sp, const float *__restrict__ fit,
                                                          const int32_t *__restrict__ valid_raw,
@@ -900,41 +921,62 @@ __global__ __launch_bounds__(kBlock) void k_fill_generic(SpaceDesc sp, const flo
                                                          int32_t *__restrict__ row_ptr,
                                                          int32_t *__restrict__ col_idx,
                                                          int32_t *__restrict__ minima) {
+    constexpr int kB = kGenericBatch;
+    __shared__ int32_t hits[kBlock][kB + 1];
     const int32_t v = blockIdx.x * kBlock + threadIdx.x;
-    const int32_t din = v < n ? in_deg[v] : 0;
-    const int32_t sink = (v < n && out_deg[v] == 0) ? 1 : 0;
+    const bool active = v < n;
+    const int32_t din = active ? in_deg[v] : 0;
+    const int32_t sink = (active && out_deg[v] == 0) ? 1 : 0;
     int32_t e_off;
     fill_rows(blockIdx.x, v, n, n_edges, din, sink, tile_eoff, tile_moff, row_ptr, minima, e_off);
-    if (v >= n || din == 0) return;
-    const uint32_t i = (uint32_t)valid_raw[v];
-    const float fv = fit[i];
+    const uint32_t i = active ? (uint32_t)valid_raw[v] : 0u;
+    const float fv = active ? fit[i] : INFINITY;   // nothing is worse than +inf
     const int32_t end = e_off + din;
     int32_t pos = e_off;
-    auto take = [&](uint32_t c) {
-        const float fc = fit[c];
-        if ((fc > fv) & (fc < INFINITY)) {
-            if (pos < end) col_idx[pos] = remap[c];
-            ++pos;
+    const int lane = threadIdx.x & 63;
+    int32_t(*mine)[kB + 1] = hits + (threadIdx.x & ~63u);
+    // candidates a0 .. a0 + kB - 1 of the parameter, those in [lo, hi) this lane's
+    auto batch = [&](uint32_t row, uint32_t st, uint32_t a0, uint32_t lo, uint32_t hi) {
+        float fc[kB];
+#pragma unroll
+        for (int u = 0; u < kB; ++u) {
+            const uint32_t a = a0 + u;
+            fc[u] = a >= lo && a < hi ? fit[row + a * st] : 0.0f;
         }
+        int32_t src[kB];
+#pragma unroll
+        for (int u = 0; u < kB; ++u) {
+            const bool worse = (fc[u] > fv) & (fc[u] < INFINITY);
+            src[u] = worse ? remap[row + (a0 + u) * st] : -1;
+        }
+        int32_t cnt = 0;
+#pragma unroll
+        for (int u = 0; u < kB; ++u)
+            if (src[u] >= 0) mine[lane][cnt++] = src[u];
+        cnt = min(cnt, end - pos);
+        if (__ballot(cnt > 0) == 0ull) return;
+        wave_lds_fence();
+#pragma unroll
+        for (int q = 0; q < 64; q += 64 / kB) {
+            const int r = q + lane / kB, h = lane % kB;
+            const int32_t rp = __shfl(pos, r, 64), rc = __shfl(cnt, r, 64);
+            if (h < rc) col_idx[rp + h] = mine[r][h];
+        }
+        wave_lds_fence();   // read before the next batch's hits are stored
+        pos += cnt;
     };
-    for (int k = 0; k < sp.n; ++k) {  // below i
-        const uint32_t r = (uint32_t)sp.radix[k], st = (uint32_t)sp.stride[k];
-        const uint32_t xk = (i / st) % r;
-        const uint32_t row = i - xk * st;
-        if (ADJ) {
-            if (xk > 0) take(row + (xk - 1) * st);
-        } else {
-            for (uint32_t a = 0; a < xk; ++a) take(row + a * st);
-        }
-    }
-    for (int k = sp.n - 1; k >= 0; --k) {  // above i
-        const uint32_t r = (uint32_t)sp.radix[k], st = (uint32_t)sp.stride[k];
-        const uint32_t xk = (i / st) % r;
-        const uint32_t row = i - xk * st;
-        if (ADJ) {
-            if (xk + 1 < r) take(row + (xk + 1) * st);
-        } else {
-            for (uint32_t a = xk + 1; a < r; ++a) take(row + a * st);
+    for (int pass = 0; pass < 2; ++pass) {   // below i: parameters 0 .. n-1; above i: n-1 .. 0
+        for (int kk = 0; kk < sp.n; ++kk) {
+            const int k = pass == 0 ? kk : sp.n - 1 - kk;
+            const uint32_t r = (uint32_t)sp.radix[k], st = (uint32_t)sp.stride[k];
+            const uint32_t xk = (i / st) % r;
+            const uint32_t row = i - xk * st;
+            uint32_t lo = pass == 0 ? 0u : xk + 1u, hi = pass == 0 ? xk : r;
+            if (ADJ) {
+                lo = pass == 0 ? (xk > 0 ? xk - 1u : 0u) : xk + 1u;
+                hi = pass == 0 ? xk : min(xk + 2u, r);
+            }
+            for (uint32_t a0 = 0; a0 < r; a0 += kB) batch(row, st, a0, lo, hi);
         }
     }
 }
@@ -1122,21 +1164,22 @@ __device__ __forceinline__ int32_t peek_stop(const PrState *st) {
 }
 
 // Workgroup 0 of sweep j >= 1: reduce the partial triples of sweep j - 1
-// in a fixed order (thread t sums parts t, t + kBlock, ...; then a fixed
+// in a fixed order (thread t sums parts t, t + B, ...; then a fixed
 // tree) and do its step.  Sweep j - 1 wrote sum w_j, the residual
 // |r_{j-1} - r_{j-2}| (zero for j = 1) and the sink part of sum w_j; for
 // the exact method, sum y_j, |y_j - y_{j-1}| and the sink part.
+template <int B = kBlock>
 __device__ void lag_step(const PrArgs &a) {
     const int32_t j = a.sweep;
     const int64_t stride = a.part_stride;
     const double *__restrict__ p = a.partials + (int64_t)((j - 1) & 1) * 3 * stride;
     constexpr int kU = 8;   // 24 loads in flight: one round covers 2048 workgroups
     double r0 = 0.0, r1 = 0.0, r2 = 0.0;
-    for (int32_t i0 = 0; i0 < a.n_parts; i0 += kU * kBlock) {
+    for (int32_t i0 = 0; i0 < a.n_parts; i0 += kU * B) {
         double v[3][kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const int32_t i = i0 + u * kBlock + (int32_t)threadIdx.x;
+            const int32_t i = i0 + u * B + (int32_t)threadIdx.x;
             const bool ok = i < a.n_parts;
             v[0][u] = ok ? p[i] : 0.0;
             v[1][u] = ok ? p[stride + i] : 0.0;
@@ -1149,7 +1192,7 @@ __device__ void lag_step(const PrArgs &a) {
             r2 += v[2][u];
         }
     }
-    block_sum3(r0, r1, r2);
+    block_sum3<B>(r0, r1, r2);
     if (threadIdx.x != 0) return;
     PrState *st = a.st;
     if (a.exact) {
@@ -1194,8 +1237,9 @@ __device__ void lag_step(const PrArgs &a) {
 }
 
 // One partial triple per workgroup (lagged step), to buffer sweep & 1.
+template <int B = kBlock>
 __device__ __forceinline__ void write_lag_partials(const PrArgs &a, double ps, double pr, double pk) {
-    block_sum3(ps, pr, pk);
+    block_sum3<B>(ps, pr, pk);
     if (threadIdx.x == 0) {
         const int64_t stride = a.part_stride;
         double *pp = a.partials + (int64_t)(a.sweep & 1) * 3 * stride + blockIdx.x;
@@ -1426,69 +1470,73 @@ __global__ __launch_bounds__(kBlock) void k_pr_iter_csr(PrArgs a) {
 // Rows binned by in-degree (BinTable): each class of buckets has its own lanes
 // per row L and T blocks of kBlock / L rows per tile.  A row's terms are
 // gathered through the CSR exactly as in k_pr_iter_csr<L> and reduced over
-// its L lanes with shuffles; x is indexed by node id.
+// its L lanes with the same tree; x is indexed by node id.
+
+// Sum over the L lanes of a row, valid in each of them: the tree of
+// __shfl_xor from L / 2 down to 1 (same pairs, so the same bits).  Below 16
+// lanes as DPP operands of the additions: after a step the lanes o apart
+// hold equal values, so a rotation by o / 2 within the row of 16 pairs the
+// same values as the exchange.
+template <int L>
+__device__ __forceinline__ float row_sum(float v) {
+    if (L >= 64) v += __shfl_xor(v, 32, 64);
+    if (L >= 32) v += __shfl_xor(v, 16, 64);
+    if (L >= 16) v += dpp_move<0x128>(v);                      // row_ror:8
+    if (L >= 16) v += dpp_move<0x124>(v);                      // row_ror:4
+    if (L == 8) v += dpp_move<0x141>(dpp_move<0x1b>(v));       // half mirror of a reversed quad: lane ^ 4
+    if (L >= 4) v += dpp_move<0x4e>(v);                        // quad_perm [2,3,0,1]
+    if (L >= 2) v += dpp_move<0xb1>(v);                        // quad_perm [1,0,3,2]
+    return v;
+}
+
+// The in-edge sum of CSR row [e0, e1), lane `lane` of L: its terms e0 + lane,
+// + L, ... in order, four rounds of loads in flight, then the tree.
+template <int L>
+__device__ __forceinline__ float row_gather(const int32_t *__restrict__ col_idx, const float *__restrict__ x,
+                                            int32_t e0, int32_t e1, int lane) {
+    float acc = 0.0f;
+    for (int32_t e = e0 + lane; e < e1; e += 4 * L) {
+        int32_t cix[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) cix[u] = e + u * L < e1 ? col_idx[e + u * L] : -1;
+        float xv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) xv[u] = cix[u] >= 0 ? x[cix[u]] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc += xv[u];
+    }
+    return row_sum<L>(acc);
+}
 
 struct BinSweep {
     const int32_t *row_ptr, *col_idx, *out_deg, *rows;
     const float *y_in, *x_in;
     float *y_out, *x_out;
     double s, c, sd;
-    LagTerms lt;   // lagged step only
 };
 
-template <int L, bool LAG>
+template <int L>
 __device__ __forceinline__ void binned_block(const BinSweep &q, int32_t first, int32_t count, double &ps,
                                              double &pr, double &pk) {
     const int lane = threadIdx.x % L;
     const int32_t r = first + (int32_t)(threadIdx.x / L);
     const bool live = r < count;
     const int32_t v = live ? q.rows[r] : 0;
-    float acc = 0.0f;
-    // lagged step: the row's own values, loaded ahead of its gathers
-    int32_t ldeg = 0;
-    float yin = 0.0f, yprev = 0.0f, gv = 0.0f;
-    if (LAG && lane == 0 && live) {
-        ldeg = q.out_deg[v];
-        yin = q.y_in[v];
-        yprev = q.lt.y_prev[v];
-        gv = q.lt.g[v];
-    }
-    if (live) {
-        const int32_t e1 = q.row_ptr[v + 1];
-        for (int32_t e = q.row_ptr[v] + lane; e < e1; e += 4 * L) {
-            int32_t cix[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) cix[u] = e + u * L < e1 ? q.col_idx[e + u * L] : -1;
-            float xv[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) xv[u] = cix[u] >= 0 ? q.x_in[cix[u]] : 0.0f;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc += xv[u];
-        }
-    }
-#pragma unroll
-    for (int o = L / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    const float acc = row_gather<L>(q.col_idx, q.x_in, live ? q.row_ptr[v] : 0, live ? q.row_ptr[v + 1] : 0, lane);
     if (lane == 0 && live) {
-        if (LAG) {
-            const float yf = lag_node(q.lt, v, acc, yin, yprev, gv, ldeg, ps, pr, pk);
-            q.y_out[v] = yf;
-            q.x_out[v] = ldeg > 0 ? yf / (float)ldeg : 0.0f;
-        } else {
-            const int32_t deg = q.out_deg[v];
-            const float yf = (float)(q.sd * (double)acc + q.c);
-            q.y_out[v] = yf;
-            q.x_out[v] = deg > 0 ? yf / (float)deg : 0.0f;
-            ps += (double)yf;
-            pr += fabs((double)yf - q.s * (double)q.y_in[v]);
-            if (deg == 0) pk += (double)yf;
-        }
+        const int32_t deg = q.out_deg[v];
+        const float yf = (float)(q.sd * (double)acc + q.c);
+        q.y_out[v] = yf;
+        q.x_out[v] = deg > 0 ? yf / (float)deg : 0.0f;
+        ps += (double)yf;
+        pr += fabs((double)yf - q.s * (double)q.y_in[v]);
+        if (deg == 0) pk += (double)yf;
     }
 }
 
 // Tile t (0 <= t < table.tiles) of a binned sweep: its class, then T blocks,
 // their terms added to ps, pr, pk.  The table is read in place (kernel
 // arguments or the member table) through the scalar unit.
-template <bool LAG>
 __device__ __forceinline__ void binned_tile(const BinSweep &q0, const_ptr<BinTable> tb, int32_t t, double &ps,
                                             double &pr, double &pk) {
     int cl = 0;
@@ -1503,45 +1551,35 @@ __device__ __forceinline__ void binned_tile(const BinSweep &q0, const_ptr<BinTab
     for (int b = 0; b < blocks; ++b) {
         const int32_t first = (lt * blocks + b) * (kBlock / lanes);
         switch (lanes) {
-            case 1: binned_block<1, LAG>(q, first, rows, ps, pr, pk); break;
-            case 2: binned_block<2, LAG>(q, first, rows, ps, pr, pk); break;
-            case 4: binned_block<4, LAG>(q, first, rows, ps, pr, pk); break;
-            case 8: binned_block<8, LAG>(q, first, rows, ps, pr, pk); break;
-            case 16: binned_block<16, LAG>(q, first, rows, ps, pr, pk); break;
-            case 32: binned_block<32, LAG>(q, first, rows, ps, pr, pk); break;
-            default: binned_block<64, LAG>(q, first, rows, ps, pr, pk); break;
+            case 1: binned_block<1>(q, first, rows, ps, pr, pk); break;
+            case 2: binned_block<2>(q, first, rows, ps, pr, pk); break;
+            case 4: binned_block<4>(q, first, rows, ps, pr, pk); break;
+            case 8: binned_block<8>(q, first, rows, ps, pr, pk); break;
+            case 16: binned_block<16>(q, first, rows, ps, pr, pk); break;
+            case 32: binned_block<32>(q, first, rows, ps, pr, pk); break;
+            default: binned_block<64>(q, first, rows, ps, pr, pk); break;
         }
     }
 }
 
-// The binned sweep over the tiles of a.bins (the plan's whole table, or a
-// part of it while the autotuner times one class).  LAG: the lagged step.
-template <bool LAG>
+// The binned sweep with a step kernel, over the tiles of a.bins (the plan's
+// whole table, or a part of it while the autotuner times one class).
 __global__ __launch_bounds__(kBlock) void k_pr_iter_binned(PrArgs a) {
     const PrState *st = a.st;
     if (st->done) return;
-    if (LAG) {
-        if (blockIdx.x == 0 && a.sweep >= 1) lag_step(a);
-        if (!lag_has_tiles(a)) return;
-    }
-    const int32_t k = LAG ? a.sweep : st->k;
+    const int32_t k = st->k;
     BinSweep q;
     q.row_ptr = a.row_ptr;
     q.col_idx = a.col_idx;
     q.out_deg = a.out_deg;
     q.rows = a.bin_rows;
-    q.y_in = a.y[LAG ? k % 3 : k & 1];
+    q.y_in = a.y[k & 1];
     q.x_in = a.x[k & 1];
-    q.y_out = a.y[LAG ? (k + 1) % 3 : (k + 1) & 1];
+    q.y_out = a.y[(k + 1) & 1];
     q.x_out = a.x[(k + 1) & 1];
-    if (LAG) {
-        q.s = q.c = q.sd = 0.0;
-        q.lt = lag_terms(a);
-    } else {
-        q.s = st->s;
-        q.c = st->c;
-        q.sd = q.s * a.d;
-    }
+    q.s = st->s;
+    q.c = st->c;
+    q.sd = q.s * a.d;
     // Every class's tiles are dealt to the XCDs in eighths, XCD j taking the
     // j-th eighth of each class in turn: a class's rows ascend in node id,
     // so an XCD works in about the j-th eighth of the nodes whatever the
@@ -1549,29 +1587,193 @@ __global__ __launch_bounds__(kBlock) void k_pr_iter_binned(PrArgs a) {
     const const_ptr<BinTable> tb = &kernel_arg<PrArgs>()->bins;
     const int xcd = blockIdx.x % kXcds, nb = gridDim.x / kXcds, l = blockIdx.x / kXcds;
     const int nc = tb->n_classes;
-    double ws = 0.0, wr = 0.0, wk = 0.0;   // lagged step: the workgroup's sums
-    bool stopped = false;                  // lagged step: the stop flag was seen (per wave)
-    for (int cl = 0; cl < nc && !stopped; ++cl) {
+    for (int cl = 0; cl < nc; ++cl) {
         const int32_t t0 = tb->c[cl].tile_begin;
         const int32_t ct = (cl + 1 < nc ? tb->c[cl + 1].tile_begin : a.bins.tiles) - t0;
         const int32_t per = (ct + kXcds - 1) / kXcds;
         const int32_t lo = t0 + per * xcd, hi = t0 + min(per * (xcd + 1), ct);
         for (int32_t t = lo + l; t < hi; t += nb) {
-            if (LAG) {
-                const int32_t stop = peek_stop(a.st);
-                binned_tile<true>(q, tb, t, ws, wr, wk);
-                if (stop) {   // per wave: no barrier in the tile loop
-                    stopped = true;
-                    break;
-                }
-            } else {
-                double ps = 0.0, pr = 0.0, pk = 0.0;
-                binned_tile<false>(q, tb, t, ps, pr, pk);
-                write_partials(a.partials, t, ps, pr, pk);
-            }
+            double ps = 0.0, pr = 0.0, pk = 0.0;
+            binned_tile(q, tb, t, ps, pr, pk);
+            write_partials(a.partials, t, ps, pr, pk);
         }
     }
-    if (LAG) write_lag_partials(a, ws, wr, wk);
+}
+
+// ---------------------------------------------------------------------------
+// The binned sweep with the lagged step, by panels: panel_rows(L) consecutive
+// rows of a class go through one workgroup of 8 waves.  A panel's row bounds
+// and own values are loaded one row per thread, coalesced; the waves then take
+// its rows in turn, so that the waves of a CU gather for neighbouring nodes at
+// the same time and share x lines in L1; the row sums go back through LDS and
+// every thread updates its own row.
+//
+// Bound by the gathers: about one cache line per edge, whatever the split.
+// At radices 64,56,40,3 (350 k nodes, 26 M edges, 54 sweeps) a sweep went from
+// 155 us to 58: the tiles it replaces (256 / L rows, a wave per long row,
+// neighbouring tiles on different CUs) waited on four dependent loads per row
+// and did each row's FP64 update on one lane of 64, and fetched most x lines
+// from L2 anew.  Counters: 25.5 M line accesses, 77 % served by L1, address
+// unit 55 % busy (one access per cycle would take 42 us).  Measured against
+// it: 4 waves per workgroup 66, panels of half the rows 63, of twice 68.
+
+// Rows of a panel: about the same number of in-edges whatever the lanes per
+// row, at most one row per thread.
+__host__ __device__ constexpr int panel_rows(int lanes) { return lanes >= 64 ? 128 : lanes >= 16 ? 256 : kPanelBlock; }
+
+struct PanelRows {
+    int32_t begin[kPanelBlock], end[kPanelBlock];
+    float acc[kPanelBlock];
+};
+
+// Rows of 64 lanes, kLongRows of them at once per wave.  The row bounds are
+// uniform, so a row's terms come through a buffer descriptor that ends with
+// the row: a lane past it reads column 0, whose x it then leaves out.  No lane
+// is masked, so the loads of all the rows are in flight together (under
+// execution masks each row waited for its own: 63 us a sweep; 2 rows at once
+// 62, 3 rows 60, 4 rows 58; more would lower the occupancy below 6).
+constexpr int kLongRows = 4;
+__device__ __forceinline__ void panel_sums_long(PanelRows &p, const int32_t *__restrict__ col_idx,
+                                                const float *__restrict__ x, int32_t count) {
+    constexpr int kWaves = kPanelBlock / 64, R = kLongRows;
+    const int lane = threadIdx.x & 63;
+    for (int32_t r0 = (threadIdx.x >> 6) * R; r0 < count; r0 += kWaves * R) {
+        int32_t n[R], c[R][2];
+        __amdgpu_buffer_rsrc_t cr[R];
+        float xv[R][2], acc[R];
+        int32_t longest = 0;
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int32_t r = min(r0 + q, count - 1);
+            const int32_t b = __builtin_amdgcn_readfirstlane(p.begin[r]);
+            n[q] = __builtin_amdgcn_readfirstlane(p.end[r]) - b;
+            longest = max(longest, n[q]);
+            cr[q] = __builtin_amdgcn_make_buffer_rsrc((void *)(col_idx + b), (short)0, 4 * n[q], 0x00020000);
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                c[q][u] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(cr[q], 4 * lane, 256 * u, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) xv[q][u] = x[c[q][u]];
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            acc[q] = 0.0f;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) acc[q] += lane + 64 * u < n[q] ? xv[q][u] : 0.0f;
+        }
+        for (int32_t e = 128; e < longest; e += 128) {
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    c[q][u] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(cr[q], 4 * (e + lane), 256 * u, 0);
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) xv[q][u] = x[c[q][u]];
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) acc[q] += e + lane + 64 * u < n[q] ? xv[q][u] : 0.0f;
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const float t = row_sum<64>(acc[q]);
+            if (lane == 0 && r0 + q < count) p.acc[r0 + q] = t;
+        }
+    }
+}
+
+template <int L>
+__device__ __forceinline__ void panel_sums(PanelRows &p, const int32_t *__restrict__ col_idx,
+                                           const float *__restrict__ x, int32_t count) {
+    constexpr int kRowsPerStep = 64 / L, kWaves = kPanelBlock / 64;
+    const int lane = threadIdx.x % L;
+    for (int32_t r0 = (threadIdx.x >> 6) * kRowsPerStep; r0 < count; r0 += kWaves * kRowsPerStep) {
+        const int32_t r = r0 + (int32_t)(threadIdx.x & 63) / L;
+        const bool live = r < count;
+        int32_t b = live ? p.begin[r] : 0, e = live ? p.end[r] : 0;
+        if (L == 64) {
+            b = __builtin_amdgcn_readfirstlane(b);
+            e = __builtin_amdgcn_readfirstlane(e);
+        }
+        const float acc = row_gather<L>(col_idx, x, b, e, lane);
+        if (lane == 0 && live) p.acc[r] = acc;
+    }
+}
+
+__global__ __launch_bounds__(kPanelBlock) void k_pr_iter_panels(PrArgs a) {
+    __shared__ PanelRows p;
+    __shared__ int32_t sh_stop;
+    const PrState *st = a.st;
+    if (st->done) return;
+    if (blockIdx.x == 0 && a.sweep >= 1) lag_step<kPanelBlock>(a);
+    if (!lag_has_tiles(a)) return;
+    const int32_t k = a.sweep;
+    const float *__restrict__ y_in = a.y[k % 3];
+    const float *__restrict__ x_in = a.x[k & 1];
+    float *__restrict__ y_out = a.y[(k + 1) % 3];
+    float *__restrict__ x_out = a.x[(k + 1) & 1];
+    const LagTerms lt = lag_terms(a);
+    const const_ptr<BinTable> tb = &kernel_arg<PrArgs>()->bins;
+    // XCD j takes the j-th eighth of every class's panels (see
+    // k_pr_iter_binned); its workgroups take them in turn, the classes with
+    // the most lanes (the longest panels) first
+    const int xcd = blockIdx.x % kXcds, nb = gridDim.x / kXcds;
+    const int nc = tb->n_classes;
+    double ws = 0.0, wr = 0.0, wk = 0.0;
+    for (int32_t flat = blockIdx.x / kXcds;; flat += nb) {
+        int32_t at = flat, first = -1, count = 0, lanes = 0, row_begin = 0;
+        for (int cl = nc - 1; cl >= 0; --cl) {
+            const int32_t rows = tb->c[cl].rows, size = panel_rows(tb->c[cl].lanes);
+            const int32_t panels = (rows + size - 1) / size, per = (panels + kXcds - 1) / kXcds;
+            const int32_t lo = per * xcd, mine = max(min(lo + per, panels) - lo, 0);
+            if (at < mine) {
+                first = (lo + at) * size;
+                count = min(size, rows - first);
+                lanes = tb->c[cl].lanes;
+                row_begin = tb->c[cl].row_begin;
+                break;
+            }
+            at -= mine;
+        }
+        if (first < 0) break;
+        const int t = threadIdx.x;
+        if (t == 0) sh_stop = __hip_atomic_load(const_cast<int32_t *>(&st->done), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int32_t v = 0, deg = 0;
+        float yin = 0.0f, yprev = 0.0f, gv = 0.0f;
+        if (t < count) {
+            v = a.bin_rows[row_begin + first + t];
+            p.begin[t] = a.row_ptr[v];
+            p.end[t] = a.row_ptr[v + 1];
+            // the row's own values, loaded ahead of the gathers
+            deg = a.out_deg[v];
+            yin = y_in[v];
+            yprev = lt.y_prev[v];
+            gv = lt.g[v];
+        }
+        __syncthreads();
+        const int32_t stop = sh_stop;
+        switch (lanes) {
+            case 1: panel_sums<1>(p, a.col_idx, x_in, count); break;
+            case 2: panel_sums<2>(p, a.col_idx, x_in, count); break;
+            case 4: panel_sums<4>(p, a.col_idx, x_in, count); break;
+            case 8: panel_sums<8>(p, a.col_idx, x_in, count); break;
+            case 16: panel_sums<16>(p, a.col_idx, x_in, count); break;
+            case 32: panel_sums<32>(p, a.col_idx, x_in, count); break;
+            default: panel_sums_long(p, a.col_idx, x_in, count); break;
+        }
+        __syncthreads();
+        if (t < count) {
+            const float yf = lag_node(lt, v, p.acc[t], yin, yprev, gv, deg, ws, wr, wk);
+            y_out[v] = yf;
+            x_out[v] = deg > 0 ? yf / (float)deg : 0.0f;
+        }
+        if (stop) break;   // uniform: every thread read the same flag after the barrier
+    }
+    write_lag_partials<kPanelBlock>(a, ws, wr, wk);
 }
 
 // Binning of the rows: per node tile, the number of rows of each class;
@@ -1903,7 +2105,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_sweep_binned(const BatchMember
         q.c = st->c;
         q.sd = q.s * m->d;
         double ps = 0.0, pr = 0.0, pk = 0.0;
-        binned_tile<false>(q, &m->bins, tile, ps, pr, pk);
+        binned_tile(q, &m->bins, tile, ps, pr, pk);
         write_partials(m->partials, tile, ps, pr, pk);
     }
 }
@@ -2176,7 +2378,7 @@ const void *csr_sweep_kernel(const PrArgs &a, int lanes) {
 }
 
 const void *binned_sweep_kernel(bool lag) {
-    return lag ? (const void *)k_pr_iter_binned<true> : (const void *)k_pr_iter_binned<false>;
+    return lag ? (const void *)k_pr_iter_panels : (const void *)k_pr_iter_binned;
 }
 
 }  // namespace
@@ -2405,11 +2607,18 @@ hipError_t launch_pr_sweep_binned(const PrArgs &a, const BinTable &t, int grid, 
     PrArgs b = a;
     b.bins = t;
     void *args[] = {(void *)&b};
-    return hipLaunchKernel(binned_sweep_kernel(a.lag != 0), dim3(grid), dim3(kBlock), args, 0, stream);
+    return hipLaunchKernel(binned_sweep_kernel(a.lag != 0), dim3(grid), dim3(a.lag ? kPanelBlock : kBlock), args, 0,
+                           stream);
+}
+
+int32_t bin_panels(const BinTable &t) {
+    int32_t n = 0;
+    for (int c = 0; c < t.n_classes; ++c) n += (t.c[c].rows + panel_rows(t.c[c].lanes) - 1) / panel_rows(t.c[c].lanes);
+    return n;
 }
 
 hipError_t pr_binned_blocks_per_cu(int *blocks, bool lag) {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, binned_sweep_kernel(lag), kBlock, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, binned_sweep_kernel(lag), lag ? kPanelBlock : kBlock, 0);
 }
 
 hipError_t launch_bin_rows(const int32_t *row_ptr, int32_t n, const int8_t *class_of_dev, int32_t *cnt,
