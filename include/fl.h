@@ -78,7 +78,9 @@ typedef struct {
  *             fl_tune cached for the plan's shape class, else FL_ROWS_SLOTS
  *             where available, else FL_ROWS_BINNED);
  *             FL_ROWS_SLOTS = one node per lane over the in-edge slot
- *             records (needs at most 256 candidate slots per node);
+ *             records (needs at most 256 candidate slots per node), or, for
+ *             small graphs run by fl_execute, over in-edge lists with the
+ *             same sums;
  *             FL_ROWS_BINNED = the CSR with rows binned by in-degree into
  *             8 buckets (0; [2^(b-1), 2^b) for b = 1..6; 64 and more), each
  *             bucket with its own lanes per row and rows per tile (the

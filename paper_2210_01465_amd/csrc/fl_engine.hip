@@ -182,6 +182,7 @@ struct fl_plan {
     uint64_t *rec = nullptr;    // node records (in-edge slot bits, out_deg, raw index)
     uint64_t *presence = nullptr;  // per wave of 64 nodes: OR of their slot bits
     fl::SlotTable sl{};
+    fl::WaveLists lists{};      // in-edge lists of a small slot space, made by its first execute
     // power-iteration working set, allocated by the first fl_execute
     float *y[3] = {nullptr, nullptr, nullptr};   // the third for the lagged step
     float *x[2] = {nullptr, nullptr};
@@ -276,7 +277,8 @@ void release_plan_buffers(fl_plan *p) {
     DevicePool &pool = p->ctx->pool;
     void *bufs[] = {p->valid_raw, p->out_deg, p->row_ptr, p->col_idx, p->minima,  p->fit_c,
                     p->rec,       p->presence, p->y[0], p->y[1],      p->y[2],     p->x[0],
-                    p->x[1],      p->g,       p->partials, p->state,  p->d_off,    p->bin_rows};
+                    p->x[1],      p->g,       p->partials, p->state,  p->d_off,    p->bin_rows,
+                    p->lists.quad};
     for (void *b : bufs) pool.release(b);
 }
 
@@ -750,6 +752,36 @@ fl_status resolve_params(fl_ctx *ctx, const fl_plan *p, const fl_params *prm, Re
     return FL_OK;
 }
 
+// Quads per wave of a plan's in-edge lists: a node has at most as many
+// in-edges as neighbours; one group more, so that whole groups can be read.
+int64_t list_stride(const fl_plan *p) {
+    const int64_t most = p->adjacent ? p->sl.k : p->sl.k / 2;
+    return std::max<int64_t>((most + 3) / 4, fl::kListQuads) + fl::kListQuads;
+}
+int64_t list_bytes(const fl_plan *p) { return (p->n + 63) / 64 * (list_stride(p) * 64 * (int64_t)sizeof(uint4) + 4); }
+
+// Whether a slot space is swept by lists: few edges (kListEdges), and lists
+// that fit the scratch array of fl_analyze_noalloc beside everything else the
+// analysis keeps there, so that it takes the same path as fl_analyze.
+bool wants_lists(const fl_plan *p) {
+    if (p->sl.words == 0 || p->e > fl::kListEdges) return false;
+    const int64_t rest = 20 * p->n_raw + (40 + 8 * (int64_t)p->sl.words) * p->n + 4 * p->e + (int64_t(1) << 20);
+    return rest + list_bytes(p) <= (int64_t)kNoAllocScratchBytes;
+}
+
+// The lists of such a plan, made by its first execute and kept with it.
+fl_status ensure_lists(fl_ctx *ctx, fl_plan *p) {
+    if (p->lists.quad) return FL_OK;
+    const int64_t waves = (p->n + 63) / 64, stride = list_stride(p);
+    char *block = pool_alloc<char>(ctx, list_bytes(p));
+    if (!block) return fail(ctx, FL_ENOMEM, "device allocation failed");
+    p->lists.quad = reinterpret_cast<uint4 *>(block);
+    p->lists.quads = reinterpret_cast<int32_t *>(p->lists.quad + waves * stride * 64);
+    p->lists.stride = (int32_t)stride;
+    FL_HIP(fl::launch_make_lists(p->row_ptr, p->col_idx, (int32_t)p->n, p->lists, ctx->stream));
+    return FL_OK;
+}
+
 // y, x (x in raw-index space for the slot sweep) and the state of a plan;
 // lag: the third y buffer and g of the lagged step as well.
 fl_status ensure_pr_buffers(fl_ctx *ctx, fl_plan *p, bool slots, bool lag) {
@@ -763,7 +795,9 @@ fl_status ensure_pr_buffers(fl_ctx *ctx, fl_plan *p, bool slots, bool lag) {
         p->g = pool_alloc<float>(ctx, p->n);
         if (!p->y[2] || !p->g) return fail(ctx, FL_ENOMEM, "device allocation failed");
     }
-    const int64_t x_need = slots ? (p->n_raw + 3) / 4 * 4 : p->n;   // raw-index space, whole 16-byte groups
+    // raw-index space, whole 16-byte groups; node ids, and the lists' zero entry
+    int64_t x_need = slots ? (p->n_raw + 3) / 4 * 4 : p->n;
+    if (wants_lists(p)) x_need = std::max<int64_t>(x_need, p->n + 1);
     if (x_need > p->x_cap) {
         for (int j = 0; j < 2; ++j) {
             ctx->pool.release(p->x[j]);
@@ -821,16 +855,27 @@ uint64_t bin_map_for(const fl_ctx *ctx, uint64_t shape) {
 // `lanes` (FL_ROWS_SLOTS or CSR lanes per row).
 fl_status prepare_pr(fl_ctx *ctx, fl_plan *p, const Resolved &r, int lanes, PrArgs &a, int &grid,
                      int &init_grid) {
-    const int kind = is_slot_layout(lanes) ? fl::kSweepSlots : is_binned_layout(lanes) ? fl::kSweepBinned
-                                                                                      : fl::kSweepCsr;
+    int kind = is_slot_layout(lanes) ? fl::kSweepSlots : is_binned_layout(lanes) ? fl::kSweepBinned
+                                                                                : fl::kSweepCsr;
     a = PrArgs{};
     a.kind = kind;
+    a.block = fl::kBlock;
+    a.lag = r.lag ? 1 : 0;   // the occupancy query asks for the kernel that will run
     if (kind == fl::kSweepBinned) {
         const fl_status bst = ensure_binned(ctx, p, bin_map_for(ctx, shape_key(p)));
         if (bst != FL_OK) return bst;
         a.bin_rows = p->bin_rows;
         a.bins = p->bins;
-        a.lag = r.lag ? 1 : 0;   // its own kernel and workgroup size
+    }
+    fl_status st = ensure_pr_buffers(ctx, p, kind == fl::kSweepSlots, r.lag);
+    if (st != FL_OK) return st;
+    if (kind == fl::kSweepSlots && wants_lists(p)) {
+        st = ensure_lists(ctx, p);
+        if (st != FL_OK) return st;
+        kind = a.kind = fl::kSweepLists;
+        a.lists = p->lists;
+        // a space that leaves CUs idle spreads its waves over more of them
+        if (r.lag && (p->n + 63) / 64 <= fl::kLoneWaves) a.block = 64;
     }
     a.adjacent = p->adjacent;
     a.x_bytes = kind == fl::kSweepSlots ? x_bytes_of(p) : 0;
@@ -838,15 +883,16 @@ fl_status prepare_pr(fl_ctx *ctx, fl_plan *p, const Resolved &r, int lanes, PrAr
     // multiple of the XCD count so each XCD gets the same number of them
     int per_cu = 0;
     FL_HIP(fl::pr_iter_blocks_per_cu(a, p->sp, p->sl, lanes, &per_cu));
+    if (kind == fl::kSweepSlots) per_cu = std::min(per_cu, fl::kSlotWorkgroups);
     const int64_t resident =
         std::max<int64_t>(fl::kXcds, (int64_t)std::max(per_cu, 1) * ctx->num_cus / fl::kXcds * fl::kXcds);
-    const int64_t rows_per_wg = kind == fl::kSweepSlots ? fl::kBlock : (kind == fl::kSweepBinned ? 1 : fl::kBlock / lanes);
+    const int64_t rows_per_wg = kind == fl::kSweepSlots || kind == fl::kSweepLists ? a.block
+                                : kind == fl::kSweepBinned                         ? 1
+                                                                                   : fl::kBlock / lanes;
     const int64_t groups = kind == fl::kSweepBinned
                                ? std::max<int64_t>(r.lag ? fl::bin_panels(p->bins) : p->bins.tiles, 1)
                                : (p->n + rows_per_wg - 1) / rows_per_wg;
     grid = (int)std::min<int64_t>(resident, (groups + fl::kXcds - 1) / fl::kXcds * fl::kXcds);
-    fl_status st = ensure_pr_buffers(ctx, p, kind == fl::kSweepSlots, r.lag);
-    if (st != FL_OK) return st;
     // partial sums: one triple per tile (init, slot sweep) or per workgroup
     // (CSR sweep, lagged step: two buffers of them)
     const int32_t n_tiles = tiles_of(p);
@@ -866,10 +912,12 @@ fl_status prepare_pr(fl_ctx *ctx, fl_plan *p, const Resolved &r, int lanes, PrAr
     a.y[1] = p->y[1];
     a.y[2] = p->y[2];
     a.g = p->g;
-    a.lag = r.lag ? 1 : 0;
     a.sweep = 0;
     a.n_parts = grid;
     a.part_stride = grid;
+    // a grid that leaves a place free gives the step a workgroup of its own: it
+    // takes about as long as one tile (160 nodes: 5.6 -> 4.8 us a sweep)
+    a.reducer = r.lag && grid < resident ? 1 : 0;
     a.n_sinks = p->m;
     a.x[0] = p->x[0];
     a.x[1] = p->x[1];

@@ -22,6 +22,22 @@ constexpr int kXcds = 8;                          // MI355X: 8 XCDs, workgroups 
 constexpr int kBatch = 16;                        // candidate slots whose loads are issued together
 constexpr int kMaxFinishGrid = 1024;              // workgroups of the batched step kernel (grid-stride)
 constexpr int kFinishBlock = 1024;                // threads of a step kernel workgroup (1 mod 3)
+// Workgroups of the slot sweep per CU.  At the large workload (W = 2) a sweep
+// with its step kernel takes 32.6, 29.1, 28.8, 27.4 and 31.2 us with 4 to 8
+// of them, one with the lagged step 27.9, 25.2, 25.3 and 24.5 us with 4 to 7
+// (its registers allow no more): the eighth costs more in L1 lines than its
+// loads in flight gain.
+constexpr int kSlotWorkgroups = 7;
+constexpr int kListQuads = 4;                     // quads of a wave's in-edge lists read at once (16 steps)
+// List sweeps of at most this many waves run one per workgroup, over as many
+// CUs as there are (7.9 k nodes, 171 k edges: 4.6 us against 5.7 with four per
+// workgroup; 125 k nodes 6.2 : 6.6).
+constexpr int kLoneWaves = 2048;
+// Slot spaces of at most this many edges are swept by in-edge lists.  Per
+// sweep, lists against slots: 18 k nodes, 44 k edges 3.9 : 5.1 us; 124 k, 1.2 M
+// 6.8 : 7.4; 373 k, 1.5 M 8.7 : 8.6; 215 k, 3.7 M 14.3 : 9.6; 886 k, 15 M
+// 38.6 : 19.7.
+constexpr int64_t kListEdges = 7 << 18;
 constexpr int kPanelBlock = 512;                  // threads of a workgroup of the lagged binned sweep (8 waves)
 constexpr int kFillStage = 6144;                  // col_idx entries of a tile assembled in LDS by the fill
 constexpr int kSmallTiles = 16;                   // batch members of at most this many tiles iterate in one workgroup
@@ -120,9 +136,10 @@ struct PrState {
     double score_den;    // sum of ranks over L
     // Lagged step (PrArgs::lag): sweep j adds the teleport-and-sink term of
     // r_{j-1}, gam[j & 1][0], and the residual of r_j against r_{j-1} uses
-    // gam[j & 1][1] as well (the term of r_{j-2}); the result is the iterate
+    // gam[j & 1][1] as well (the term of r_{j-2}); gam[j & 1][2] is
+    // gam[j & 1][0] over the initial iterate 1/N; the result is the iterate
     // r = w + out_gamma in y buffer out_buf, whose entries sum to out_sigma.
-    double gam[2][2];
+    double gam[2][3];
     double out_gamma;
     double out_sigma;
     int32_t out_buf;
@@ -133,7 +150,17 @@ struct PrState {
 enum SweepKind : int32_t {
     kSweepCsr = 0,    // pull over the CSR, L lanes per row, x indexed by node id
     kSweepSlots = 1,  // pull over the records' in-edge slot bits, x indexed by raw index
-    kSweepBinned = 2  // pull over the CSR with rows binned by in-degree, each bin its own lanes per row
+    kSweepBinned = 2, // pull over the CSR with rows binned by in-degree, each bin its own lanes per row
+    kSweepLists = 3   // pull over the waves' in-edge lists, x indexed by node id (n + 1 entries, the last 0)
+};
+
+// In-edge lists per wave of 64 consecutive nodes: wave w's quad u of lane l is
+// quad[(w * stride + u) * 64 + l], four byte offsets into x; quads[w] of them
+// are used, a positive multiple of kListQuads.
+struct WaveLists {
+    uint4 *quad;
+    int32_t *quads;
+    int32_t stride;
 };
 
 // Rows binned by in-degree: bucket 0 holds in-degree 0, bucket b >= 1 the
@@ -162,7 +189,17 @@ __host__ __device__ inline int bucket_of(int32_t deg) {
     return b;
 }
 
+// Buffers of one sweep of the lagged step: sweep j reads w_j, w_{j-1} and the
+// partial sums of sweep j - 1, and writes w_{j+1}.
+struct LagBuffers {
+    const float *y_in, *y_prev, *x_in;
+    float *y_out, *x_out;
+    const double *part_in;
+    double *part_out;
+};
+
 struct PrArgs {
+    LagBuffers cur;         // set for every launch of a lagged sweep
     const int32_t *row_ptr;
     const int32_t *col_idx;
     const int32_t *out_deg;
@@ -186,6 +223,7 @@ struct PrArgs {
     int32_t x_bytes;        // slot sweep: bytes its buffer loads span (x from the most negative slot
                             // offset to the end plus the largest), when < 2^31; else 0 (plain loads)
     int32_t exact;          // 1: Jacobi sweeps u <- 1 + d P u to an exact fixed point (s = c = 1)
+    WaveLists lists;          // list sweep
     const int32_t *bin_rows;  // binned sweep: node ids grouped by class
     BinTable bins;            // binned sweep: classes and tiles
     // Lagged step (lag != 0): the sweeps run back to back with no step
@@ -203,6 +241,8 @@ struct PrArgs {
     int32_t sweep;
     int32_t n_parts;
     int32_t part_stride;
+    int32_t block;     // threads per workgroup of the sweep (list sweep: 64 or kBlock; else kBlock)
+    int32_t reducer;   // 1: the step has a workgroup of its own (the first of grid + 1)
     int64_t n_sinks;
     float *g;
 };
@@ -274,6 +314,8 @@ hipError_t launch_pr_step(const PrArgs &a, int grid, hipStream_t stream);
 // Workgroups of the sweep kernel for this layout that fit on one CU at once.
 hipError_t pr_iter_blocks_per_cu(const PrArgs &a, const SpaceDesc &sp, const SlotTable &sl, int lanes,
                                  int *blocks);
+hipError_t launch_make_lists(const int32_t *row_ptr, const int32_t *col_idx, int32_t n, const WaveLists &wl,
+                             hipStream_t stream);
 hipError_t launch_pr_output(const PrArgs &a, double *pagerank, hipStream_t stream);
 // Binning of the rows by in-degree class: class_of[b] is the class of bucket
 // b.  Count per (class, node tile) into cnt (kBuckets x n_tiles, class-major),

@@ -47,17 +47,95 @@ __device__ __forceinline__ const_ptr<T> kernel_arg() {
     return (const_ptr<T>)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
+// The two halves of the exchange "lane ^ 32" (or ^ 16) of x: in every lane
+// (own, other) in one order or the other, so that a sum of the two equals
+// x + __shfl_xor(x, 32) (16).
+__device__ __forceinline__ void exchange32(uint32_t x, uint32_t &a, uint32_t &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    a = r[0];
+    b = r[1];
+}
+__device__ __forceinline__ void exchange16(uint32_t x, uint32_t &a, uint32_t &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    a = r[0];
+    b = r[1];
+}
+
+// The value of another lane, as a DPP operand (CTRL: the DPP control).
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x) {
+    return __uint_as_float(dpp_move<CTRL>(__float_as_uint(x)));
+}
+template <int CTRL>
+__device__ __forceinline__ int32_t dpp_move(int32_t x) {
+    return (int32_t)dpp_move<CTRL>((uint32_t)x);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    return __builtin_bit_cast(double, ((uint64_t)dpp_move<CTRL>((uint32_t)(u >> 32)) << 32) | dpp_move<CTRL>((uint32_t)u));
+}
+
+__device__ __forceinline__ void exchange(float x, int o, float &a, float &b) {
+    uint32_t p, q;
+    if (o == 32) exchange32(__float_as_uint(x), p, q);
+    else exchange16(__float_as_uint(x), p, q);
+    a = __uint_as_float(p);
+    b = __uint_as_float(q);
+}
+__device__ __forceinline__ void exchange(double x, int o, double &a, double &b) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    uint32_t pl, ql, ph, qh;
+    if (o == 32) {
+        exchange32((uint32_t)u, pl, ql);
+        exchange32((uint32_t)(u >> 32), ph, qh);
+    } else {
+        exchange16((uint32_t)u, pl, ql);
+        exchange16((uint32_t)(u >> 32), ph, qh);
+    }
+    a = __builtin_bit_cast(double, ((uint64_t)ph << 32) | pl);
+    b = __builtin_bit_cast(double, ((uint64_t)qh << 32) | ql);
+}
+
+// Sum over the 64 lanes, valid in each: the tree of __shfl_xor from 32 down
+// to 1 (same pairs, so the same bits), as vector instructions.  Below 16
+// lanes the other lane's value is a DPP operand: after a step the lanes o
+// apart hold equal values, so a rotation by o / 2 within the row of 16 pairs
+// the same values as the exchange.
 template <typename T>
 __device__ __forceinline__ T wave_sum(T x) {
+    T a, b;
+    exchange(x, 32, a, b);
+    x = a + b;
+    exchange(x, 16, a, b);
+    x = a + b;
+    x += dpp_move<0x128>(x);   // row_ror:8
+    x += dpp_move<0x124>(x);   // row_ror:4
+    x += dpp_move<0x4e>(x);    // quad_perm [2,3,0,1]
+    x += dpp_move<0xb1>(x);    // quad_perm [1,0,3,2]
+    return x;
+}
+template <>
+__device__ __forceinline__ int32_t wave_sum(int32_t x) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    return x;
+}
+template <>
+__device__ __forceinline__ int64_t wave_sum(int64_t x) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
     return x;
 }
 
-// The value of another lane, as a DPP operand (CTRL: the DPP control).
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float x) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, true));
+__device__ __forceinline__ int32_t wave_max(int32_t x) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x = max(x, __shfl_xor(x, o, 64));
+    return x;
 }
 
 __device__ __forceinline__ float wave_min(float x) {
@@ -1065,16 +1143,6 @@ __device__ void finish_step(PrState *st, const double *__restrict__ partials, in
     double s1 = c0 == 1 ? r[0] : (c0 == 0 ? r[1] : r[2]);
     double s2 = c0 == 2 ? r[0] : (c0 == 1 ? r[1] : r[2]);
     block_sum3<B>(s0, s1, s2);
-    if (first && threadIdx.x == 0) {
-        // lagged step: r_0 = w_0 (no constant term), so sweep 0 adds nothing
-        // and sweep 1 adds gamma_0 = (d sink(r_0) + 1 - d) / N
-        st->gam[0][0] = st->gam[0][1] = 0.0;
-        st->gam[1][0] = exact ? 0.0 : (d * s2 + (1.0 - d)) / (double)n;
-        st->gam[1][1] = 0.0;
-        st->out_buf = 0;
-        st->out_gamma = 0.0;
-        st->out_sigma = s0;
-    }
     if (exact && threadIdx.x == 0) {
         // Jacobi sweeps y' = d P y + 1 (the sweep computes s d acc + c with
         // s = c = 1); a sweep that changes no value ends them, and s then
@@ -1158,21 +1226,26 @@ __device__ __forceinline__ void set_stop(PrState *st, int32_t v) {
     __hip_atomic_store(&st->done, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Issued ahead of a tile; stop_seen after it waits for the value (a test
+// ahead of the tile would add the load's latency to it).
 __device__ __forceinline__ int32_t peek_stop(const PrState *st) {
-    return __builtin_amdgcn_readfirstlane(
-        __hip_atomic_load(const_cast<int32_t *>(&st->done), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    return __hip_atomic_load(const_cast<int32_t *>(&st->done), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ bool stop_seen(int32_t peeked) { return __builtin_amdgcn_readfirstlane(peeked) != 0; }
 
 // Workgroup 0 of sweep j >= 1: reduce the partial triples of sweep j - 1
 // in a fixed order (thread t sums parts t, t + B, ...; then a fixed
 // tree) and do its step.  Sweep j - 1 wrote sum w_j, the residual
 // |r_{j-1} - r_{j-2}| (zero for j = 1) and the sink part of sum w_j; for
 // the exact method, sum y_j, |y_j - y_{j-1}| and the sink part.
+// The initial iterate 1/N, rounded to FP32.
+__device__ __forceinline__ double lag_y0(int32_t n) { return (double)(float)(1.0 / (double)n); }
+
 template <int B = kBlock>
 __device__ void lag_step(const PrArgs &a) {
     const int32_t j = a.sweep;
     const int64_t stride = a.part_stride;
-    const double *__restrict__ p = a.partials + (int64_t)((j - 1) & 1) * 3 * stride;
+    const double *__restrict__ p = a.cur.part_in;
     constexpr int kU = 8;   // 24 loads in flight: one round covers 2048 workgroups
     double r0 = 0.0, r1 = 0.0, r2 = 0.0;
     for (int32_t i0 = 0; i0 < a.n_parts; i0 += kU * B) {
@@ -1230,19 +1303,21 @@ __device__ void lag_step(const PrArgs &a) {
             set_stop(st, stop);
         }
     }
-    st->gam[(j + 1) & 1][0] = (a.d * sink + (1.0 - a.d)) / n;   // gamma_j
+    const double gj = (a.d * sink + (1.0 - a.d)) / n;   // gamma_j
+    st->gam[(j + 1) & 1][0] = gj;
     st->gam[(j + 1) & 1][1] = ga;
+    st->gam[(j + 1) & 1][2] = gj / lag_y0(a.n);
     st->sigma = sig;
     st->sink = sink;
 }
 
 // One partial triple per workgroup (lagged step), to buffer sweep & 1.
 template <int B = kBlock>
-__device__ __forceinline__ void write_lag_partials(const PrArgs &a, double ps, double pr, double pk) {
+__device__ __forceinline__ void write_lag_partials(const PrArgs &a, int b, double ps, double pr, double pk) {
     block_sum3<B>(ps, pr, pk);
     if (threadIdx.x == 0) {
         const int64_t stride = a.part_stride;
-        double *pp = a.partials + (int64_t)(a.sweep & 1) * 3 * stride + blockIdx.x;
+        double *pp = a.cur.part_out + b;
         pp[0] = ps;
         pp[stride] = pr;
         pp[2 * stride] = pk;
@@ -1262,15 +1337,17 @@ struct LagTerms {
 __device__ __forceinline__ LagTerms lag_terms(const PrArgs &a) {
     LagTerms t;
     const int32_t j = a.sweep;
-    t.y_prev = a.y[(j + 2) % 3];
+    t.y_prev = a.cur.y_prev;
     t.g = a.g;
     t.d = a.d;
     t.mode = a.exact ? kLagExact : (j == 0 ? kLagFirst : kLagNext);
+    // vector loads: through the scalar unit the compiler loads them again in
+    // every tile, from lines the step is writing (25 -> 30 us a sweep at the
+    // large workload)
     const PrState *st = a.st;
     t.ga = st->gam[j & 1][0];
     t.gb = st->gam[j & 1][1];
-    const double y0 = (double)(float)(1.0 / (double)a.n);
-    t.gs = t.ga / y0;
+    t.gs = st->gam[j & 1][2];
     return t;
 }
 
@@ -1278,6 +1355,17 @@ __device__ __forceinline__ LagTerms lag_terms(const PrArgs &a) {
 // the cap allows only does the step of the one before.
 __device__ __forceinline__ bool lag_has_tiles(const PrArgs &a) {
     return a.sweep <= a.max_iter - (a.exact ? 1 : 0);
+}
+
+// The index of this workgroup among those that walk a lagged sweep's tiles
+// (n_parts of them), or -1 if it has none.  The step of the sweep before is
+// done by the first workgroup ahead of its tiles, or, with a.reducer, by a
+// workgroup of its own.
+template <int B = kBlock>
+__device__ __forceinline__ int lag_workgroup(const PrArgs &a) {
+    if (blockIdx.x == 0 && a.sweep >= 1) lag_step<B>(a);
+    const int wg = (int)blockIdx.x - a.reducer;
+    return lag_has_tiles(a) ? wg : -1;
 }
 
 // The new value of node v in a lagged sweep from its edge sum acc, its terms
@@ -1323,6 +1411,7 @@ __device__ __forceinline__ void init_tile(int32_t tile, int32_t n, const int32_t
 }
 
 __global__ __launch_bounds__(kBlock) void k_pr_init(PrArgs a) {
+    if (a.kind == kSweepLists && blockIdx.x == 0 && threadIdx.x == 0) a.x[0][a.n] = a.x[1][a.n] = 0.0f;
     const int32_t n_tiles = (a.n + kBlock - 1) / kBlock;
     for (int32_t t = blockIdx.x; t < n_tiles; t += gridDim.x)
         init_tile(t, a.n, a.out_deg, a.kind == kSweepSlots ? a.valid_raw : nullptr, a.y[0], a.x[0], a.partials);
@@ -1341,6 +1430,7 @@ __global__ __launch_bounds__(kBlock) void k_pr_init_lag(PrArgs a) {
         a.x[0][xmap ? xmap[v] : v] = deg > 0 ? y0 / (float)deg : 0.0f;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (a.kind == kSweepLists) a.x[0][a.n] = a.x[1][a.n] = 0.0f;
         PrState *st = a.st;
         const double y = (double)y0, n = (double)a.n;
         const double s0 = n * y, s2 = (double)a.n_sinks * y;
@@ -1354,9 +1444,10 @@ __global__ __launch_bounds__(kBlock) void k_pr_init_lag(PrArgs a) {
         st->resid = 0.0;
         st->resid_prev = 0.0;
         // sweep 0 adds nothing (r_0 = w_0), sweep 1 adds gamma_0
-        st->gam[0][0] = st->gam[0][1] = 0.0;
+        st->gam[0][0] = st->gam[0][1] = st->gam[0][2] = 0.0;
         st->gam[1][0] = a.exact ? 0.0 : (a.d * s2 + (1.0 - a.d)) / n;
         st->gam[1][1] = 0.0;
+        st->gam[1][2] = st->gam[1][0] / y;
         st->out_buf = 0;
         st->out_gamma = 0.0;
         st->out_sigma = s0;
@@ -1369,12 +1460,13 @@ __global__ __launch_bounds__(kBlock) void k_pr_init_lag(PrArgs a) {
 // gathers stay in its L2.
 struct TileWalk {
     int32_t first, end, step;
-    __device__ TileWalk(int32_t n_tiles) {
-        const int g = gridDim.x;
-        const int xcd = blockIdx.x % kXcds;
+    __device__ explicit TileWalk(int32_t n_tiles) : TileWalk(n_tiles, (int)blockIdx.x, (int)gridDim.x) {}
+    // workgroup b of the g that walk the tiles
+    __device__ TileWalk(int32_t n_tiles, int b, int g) {
+        const int xcd = b % kXcds;
         const int32_t per = (n_tiles + kXcds - 1) / kXcds;
         const int32_t lo = per * xcd, hi = min(per * (xcd + 1), n_tiles);
-        const int nb = g / kXcds, l = blockIdx.x / kXcds;
+        const int nb = g / kXcds, l = b / kXcds;
         first = lo + l;
         end = hi;
         step = nb;
@@ -1400,15 +1492,13 @@ template <int L, bool LAG>
 __global__ __launch_bounds__(kBlock) void k_pr_iter_csr(PrArgs a) {
     const PrState *st = a.st;
     if (st->done) return;
-    if (LAG) {
-        if (blockIdx.x == 0 && a.sweep >= 1) lag_step(a);
-        if (!lag_has_tiles(a)) return;
-    }
+    const int wg = LAG ? lag_workgroup(a) : (int)blockIdx.x;
+    if (LAG && wg < 0) return;
     const int32_t k = LAG ? a.sweep : st->k;
-    const float *__restrict__ y_in = a.y[LAG ? k % 3 : k & 1];
-    const float *__restrict__ x_in = a.x[k & 1];
-    float *__restrict__ y_out = a.y[LAG ? (k + 1) % 3 : (k + 1) & 1];
-    float *__restrict__ x_out = a.x[(k + 1) & 1];
+    const float *__restrict__ y_in = LAG ? a.cur.y_in : a.y[k & 1];
+    const float *__restrict__ x_in = LAG ? a.cur.x_in : a.x[k & 1];
+    float *__restrict__ y_out = LAG ? a.cur.y_out : a.y[(k + 1) & 1];
+    float *__restrict__ x_out = LAG ? a.cur.x_out : a.x[(k + 1) & 1];
     LagTerms lt{};
     if (LAG) lt = lag_terms(a);
     const int32_t *__restrict__ row_ptr = a.row_ptr;
@@ -1418,7 +1508,7 @@ __global__ __launch_bounds__(kBlock) void k_pr_iter_csr(PrArgs a) {
     constexpr int kRows = kBlock / L;
     const int lane = threadIdx.x % L;
     const int sub = threadIdx.x / L;
-    const TileWalk w((a.n + kRows - 1) / kRows);
+    const TileWalk w((a.n + kRows - 1) / kRows, wg, LAG ? a.n_parts : (int)gridDim.x);
     double ps = 0.0, pr = 0.0, pk = 0.0;
     for (int32_t t = w.first; t < w.end; t += w.step) {
         const int32_t stop = LAG ? peek_stop(a.st) : 0;
@@ -1457,10 +1547,10 @@ __global__ __launch_bounds__(kBlock) void k_pr_iter_csr(PrArgs a) {
                 pr_node_update(a, v, v, acc, sd, c, s, y_in, y_out, x_out, ps, pr, pk);
             }
         }
-        if (stop) break;   // lagged step, per wave: this loop has no barrier
+        if (LAG && stop_seen(stop)) break;   // per wave: this loop has no barrier
     }
     if (LAG)
-        write_lag_partials(a, ps, pr, pk);
+        write_lag_partials(a, wg, ps, pr, pk);
     else
         write_partials(a.partials, blockIdx.x, ps, pr, pk);
 }
@@ -1472,15 +1562,18 @@ __global__ __launch_bounds__(kBlock) void k_pr_iter_csr(PrArgs a) {
 // gathered through the CSR exactly as in k_pr_iter_csr<L> and reduced over
 // its L lanes with the same tree; x is indexed by node id.
 
-// Sum over the L lanes of a row, valid in each of them: the tree of
-// __shfl_xor from L / 2 down to 1 (same pairs, so the same bits).  Below 16
-// lanes as DPP operands of the additions: after a step the lanes o apart
-// hold equal values, so a rotation by o / 2 within the row of 16 pairs the
-// same values as the exchange.
+// Sum over the L lanes of a row, valid in each of them (see wave_sum).
 template <int L>
 __device__ __forceinline__ float row_sum(float v) {
-    if (L >= 64) v += __shfl_xor(v, 32, 64);
-    if (L >= 32) v += __shfl_xor(v, 16, 64);
+    float a, b;
+    if (L >= 64) {
+        exchange(v, 32, a, b);
+        v = a + b;
+    }
+    if (L >= 32) {
+        exchange(v, 16, a, b);
+        v = a + b;
+    }
     if (L >= 16) v += dpp_move<0x128>(v);                      // row_ror:8
     if (L >= 16) v += dpp_move<0x124>(v);                      // row_ror:4
     if (L == 8) v += dpp_move<0x141>(dpp_move<0x1b>(v));       // half mirror of a reversed quad: lane ^ 4
@@ -1709,22 +1802,21 @@ __global__ __launch_bounds__(kPanelBlock) void k_pr_iter_panels(PrArgs a) {
     __shared__ int32_t sh_stop;
     const PrState *st = a.st;
     if (st->done) return;
-    if (blockIdx.x == 0 && a.sweep >= 1) lag_step<kPanelBlock>(a);
-    if (!lag_has_tiles(a)) return;
-    const int32_t k = a.sweep;
-    const float *__restrict__ y_in = a.y[k % 3];
-    const float *__restrict__ x_in = a.x[k & 1];
-    float *__restrict__ y_out = a.y[(k + 1) % 3];
-    float *__restrict__ x_out = a.x[(k + 1) & 1];
+    const int wg = lag_workgroup<kPanelBlock>(a);
+    if (wg < 0) return;
+    const float *__restrict__ y_in = a.cur.y_in;
+    const float *__restrict__ x_in = a.cur.x_in;
+    float *__restrict__ y_out = a.cur.y_out;
+    float *__restrict__ x_out = a.cur.x_out;
     const LagTerms lt = lag_terms(a);
     const const_ptr<BinTable> tb = &kernel_arg<PrArgs>()->bins;
     // XCD j takes the j-th eighth of every class's panels (see
     // k_pr_iter_binned); its workgroups take them in turn, the classes with
     // the most lanes (the longest panels) first
-    const int xcd = blockIdx.x % kXcds, nb = gridDim.x / kXcds;
+    const int xcd = wg % kXcds, nb = a.n_parts / kXcds;
     const int nc = tb->n_classes;
     double ws = 0.0, wr = 0.0, wk = 0.0;
-    for (int32_t flat = blockIdx.x / kXcds;; flat += nb) {
+    for (int32_t flat = wg / kXcds;; flat += nb) {
         int32_t at = flat, first = -1, count = 0, lanes = 0, row_begin = 0;
         for (int cl = nc - 1; cl >= 0; --cl) {
             const int32_t rows = tb->c[cl].rows, size = panel_rows(tb->c[cl].lanes);
@@ -1773,7 +1865,7 @@ __global__ __launch_bounds__(kPanelBlock) void k_pr_iter_panels(PrArgs a) {
         }
         if (stop) break;   // uniform: every thread read the same flag after the barrier
     }
-    write_lag_partials<kPanelBlock>(a, ws, wr, wk);
+    write_lag_partials<kPanelBlock>(a, wg, ws, wr, wk);
 }
 
 // Binning of the rows: per node tile, the number of rows of each class;
@@ -1991,18 +2083,16 @@ template <int W, bool BUF, bool LAG>
 __global__ __launch_bounds__(kBlock) void k_pr_iter_slots(PrArgs a) {
     const PrState *st = a.st;
     if (st->done) return;
-    if (LAG) {
-        if (blockIdx.x == 0 && a.sweep >= 1) lag_step(a);
-        if (!lag_has_tiles(a)) return;
-    }
+    const int wg = LAG ? lag_workgroup(a) : (int)blockIdx.x;
+    if (LAG && wg < 0) return;
     const int32_t k = LAG ? a.sweep : st->k;
     SweepTile q;
     q.rec = a.rec;
     q.off = to_const(a.off);
-    q.y_in = a.y[LAG ? k % 3 : k & 1];
-    q.x_in = a.x[k & 1];
-    q.y_out = a.y[LAG ? (k + 1) % 3 : (k + 1) & 1];
-    q.x_out = a.x[(k + 1) & 1];
+    q.y_in = LAG ? a.cur.y_in : a.y[k & 1];
+    q.x_in = LAG ? a.cur.x_in : a.x[k & 1];
+    q.y_out = LAG ? a.cur.y_out : a.y[(k + 1) & 1];
+    q.x_out = LAG ? a.cur.x_out : a.x[(k + 1) & 1];
     q.partials = a.partials;
     if (LAG) {
         q.s = q.c = q.sd = 0.0;
@@ -2016,7 +2106,7 @@ __global__ __launch_bounds__(kBlock) void k_pr_iter_slots(PrArgs a) {
     q.k_slots = a.k_slots;
     q.k_pad = a.k_pad;
     q.x_bytes = a.x_bytes;
-    const TileWalk w((a.n + kBlock - 1) / kBlock);
+    const TileWalk w((a.n + kBlock - 1) / kBlock, wg, LAG ? a.n_parts : (int)gridDim.x);
     if (LAG) {
         // each thread's running sums live in LDS between its tiles
         __shared__ double sums[3][kBlock];
@@ -2029,12 +2119,176 @@ __global__ __launch_bounds__(kBlock) void k_pr_iter_slots(PrArgs a) {
             sums[0][lt] += ps;
             sums[1][lt] += pr;
             sums[2][lt] += pk;
-            if (stop) break;   // per wave: this loop has no barrier
+            if (stop_seen(stop)) break;   // per wave: this loop has no barrier
         }
-        write_lag_partials(a, sums[0][lt], sums[1][lt], sums[2][lt]);
+        write_lag_partials(a, wg, sums[0][lt], sums[1][lt], sums[2][lt]);
     } else {
         for (int32_t t = w.first; t < w.end; t += w.step) sweep_tile<W, BUF>(q, t);
     }
+}
+
+// ---------------------------------------------------------------------------
+// In-edge lists of a wave of 64 consecutive nodes (WaveLists): step q of lane
+// l holds the byte offset in x of the l-th node's q-th in-edge source, in
+// ascending source order; a lane with fewer in-edges than the longest of its
+// wave names x[n], which holds 0.  Four steps of a lane are 16 bytes.
+
+// Lists from the CSR: the rows of a workgroup's four waves are one contiguous
+// piece of col_idx, copied to LDS in one pass where it fits (a piece that does
+// not is read row by row).
+__global__ __launch_bounds__(kBlock) void k_make_lists(const int32_t *__restrict__ row_ptr,
+                                                       const int32_t *__restrict__ col_idx, int32_t n,
+                                                       WaveLists wl) {
+    __shared__ int32_t stage[kFillStage];
+    const int32_t v = blockIdx.x * kBlock + threadIdx.x;
+    const int32_t first = blockIdx.x * kBlock, last = min(first + kBlock, n);
+    const int32_t e0 = row_ptr[first], count = row_ptr[last] - e0;
+    const bool staged = count <= kFillStage;
+    if (staged)
+        for (int32_t j = threadIdx.x; j < count; j += kBlock) stage[j] = col_idx[e0 + j];
+    const int32_t b = v < n ? row_ptr[v] : 0, deg = v < n ? row_ptr[v + 1] - b : 0;
+    // whole groups of the quads a sweep reads at once, at least one
+    const int32_t quads = max((wave_max(deg) + 4 * kListQuads - 1) / (4 * kListQuads), 1) * kListQuads;
+    if ((threadIdx.x & 63) == 0 && v < n) wl.quads[v >> 6] = quads;
+    __syncthreads();
+    uint4 *out = wl.quad + (int64_t)(v >> 6) * wl.stride * 64 + (threadIdx.x & 63);
+    if ((v & ~63) >= n) return;
+    for (int32_t q = 0; q < quads; ++q) {
+        uint32_t o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int32_t j = 4 * q + u;
+            int32_t c = n;
+            if (j < deg) c = staged ? stage[b - e0 + j] : col_idx[b + j];
+            o[u] = 4u * (uint32_t)c;
+        }
+        out[64 * q] = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+}
+
+// The list sweep: one node per lane, as the slot sweep, with x in node-id
+// space (n + 1 entries).  A step is one gather and one addition, with no test
+// and no mask, and the terms are added in the order of the CSR row: the same
+// FP32 sum, bit for bit.
+//
+// For graphs that leave the chip mostly idle a sweep is one wave's chain of
+// latencies: state and lists, gathers, the update, the partial sums.  The slot
+// sweep adds about 9 instructions for each candidate slot to it, most of
+// them for slots the wave does not have (92 slots: 7.1 us a sweep, lists
+// 4.6; 66 slots and 125 k nodes 7.8 : 6.2; 22 slots and 129 nodes 5.6 : 3.1).
+// For large graphs the lists lose (kListEdges): a step's gather touches about
+// 27 cache lines, since the lanes' sources lie at different slots, against 9
+// of a slot's, and the lists are read as well.
+struct ListTile {
+    const uint4 *quad;
+    const_ptr<int32_t> quads;
+    const int32_t *out_deg;
+    const float *y_in, *x_in;
+    float *y_out, *x_out;
+    double s, c, sd;
+    int32_t n, stride;
+    LagTerms lt;   // lagged step only
+};
+
+// Node v of a tile (64 consecutive ones per wave): as sweep_tile_sums.
+template <bool LAG>
+__device__ __forceinline__ void list_node_sums(const ListTile &q, int32_t v, double &ps, double &pr, double &pk) {
+    if (!LAG) ps = pr = pk = 0.0;
+    const int32_t first = __builtin_amdgcn_readfirstlane(v & ~63);
+    if (first >= q.n) return;
+    const int32_t vc = min(v, q.n - 1);
+    const uint4 *__restrict__ list = q.quad + (int64_t)(first >> 6) * q.stride * 64 + (v & 63);
+    // the first group of quads is read ahead of the wave's length (every wave
+    // has one)
+    constexpr int kQ = kListQuads;
+    uint4 o[kQ];
+#pragma unroll
+    for (int u = 0; u < kQ; ++u) o[u] = list[64 * u];
+    const int32_t deg = q.out_deg[vc];
+    float yin = q.y_in[vc], yprev = 0.0f, gv = 0.0f;
+    if (LAG) {
+        yprev = q.lt.y_prev[vc];
+        gv = q.lt.g[vc];
+    }
+    const int32_t quads = q.quads[first >> 6];
+    const __amdgpu_buffer_rsrc_t xr =
+        __builtin_amdgcn_make_buffer_rsrc((void *)q.x_in, (short)0, 4 * (q.n + 1), 0x00020000);
+    float acc = 0.0f;
+    for (int32_t c = 0; c < quads; c += kQ) {
+        float t[kQ][4];
+#pragma unroll
+        for (int u = 0; u < kQ; ++u) {
+            const uint32_t off[4] = {o[u].x, o[u].y, o[u].z, o[u].w};
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+                t[u][h] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(xr, off[h], 0, 0));
+        }
+        if (c + kQ < quads) {
+#pragma unroll
+            for (int u = 0; u < kQ; ++u) o[u] = list[64 * (c + kQ + u)];
+        }
+#pragma unroll
+        for (int u = 0; u < kQ; ++u)
+#pragma unroll
+            for (int h = 0; h < 4; ++h) acc += t[u][h];
+    }
+    // keeps their conversions to FP64, and the wait for them, behind the gathers
+    if (LAG) asm("" : "+v"(yin), "+v"(yprev), "+v"(gv));
+    if (v >= q.n) return;
+    float yf;
+    if (LAG) {
+        yf = lag_node(q.lt, v, acc, yin, yprev, gv, deg, ps, pr, pk);
+    } else {
+        yf = (float)(q.sd * (double)acc + q.c);
+        ps = (double)yf;
+        pr = fabs((double)yf - q.s * (double)yin);
+        if (deg == 0) pk = (double)yf;
+    }
+    q.y_out[v] = yf;
+    q.x_out[v] = deg > 0 ? yf / (float)deg : 0.0f;
+}
+
+template <bool LAG, int B>
+__global__ __launch_bounds__(B) void k_pr_iter_lists(PrArgs a) {
+    const PrState *st = a.st;
+    if (st->done) return;
+    const int wg = LAG ? lag_workgroup<B>(a) : (int)blockIdx.x;
+    if (LAG && wg < 0) return;
+    const int32_t k = LAG ? a.sweep : st->k;
+    ListTile q;
+    q.quad = a.lists.quad;
+    q.quads = to_const(a.lists.quads);
+    q.stride = a.lists.stride;
+    q.out_deg = a.out_deg;
+    q.y_in = LAG ? a.cur.y_in : a.y[k & 1];
+    q.x_in = LAG ? a.cur.x_in : a.x[k & 1];
+    q.y_out = LAG ? a.cur.y_out : a.y[(k + 1) & 1];
+    q.x_out = LAG ? a.cur.x_out : a.x[(k + 1) & 1];
+    q.n = a.n;
+    if (LAG) {
+        q.s = q.c = q.sd = 0.0;
+        q.lt = lag_terms(a);
+    } else {
+        q.s = st->s;
+        q.c = st->c;
+        q.sd = q.s * a.d;
+    }
+    const TileWalk w((a.n + B - 1) / B, wg, LAG ? a.n_parts : (int)gridDim.x);
+    double ws = 0.0, wr = 0.0, wk = 0.0;
+    for (int32_t t = w.first; t < w.end; t += w.step) {
+        const int32_t stop = LAG ? peek_stop(a.st) : 0;
+        double ps = 0.0, pr = 0.0, pk = 0.0;
+        list_node_sums<LAG>(q, t * B + (int)threadIdx.x, ps, pr, pk);
+        if (LAG) {
+            ws += ps;
+            wr += pr;
+            wk += pk;
+            if (stop_seen(stop)) break;   // per wave: this loop has no barrier
+        } else {
+            write_partials(a.partials, t, ps, pr, pk);
+        }
+    }
+    if (LAG) write_lag_partials<B>(a, wg, ws, wr, wk);
 }
 
 // ---------------------------------------------------------------------------
@@ -2377,6 +2631,11 @@ const void *csr_sweep_kernel(const PrArgs &a, int lanes) {
     return a.lag ? csr_sweep_fn<true>(lanes) : csr_sweep_fn<false>(lanes);
 }
 
+const void *list_sweep_kernel(const PrArgs &a) {
+    if (!a.lag) return (const void *)k_pr_iter_lists<false, kBlock>;
+    return a.block == 64 ? (const void *)k_pr_iter_lists<true, 64> : (const void *)k_pr_iter_lists<true, kBlock>;
+}
+
 const void *binned_sweep_kernel(bool lag) {
     return lag ? (const void *)k_pr_iter_panels : (const void *)k_pr_iter_binned;
 }
@@ -2597,18 +2856,36 @@ hipError_t pr_iter_blocks_per_cu(const PrArgs &a, const SpaceDesc &sp, const Slo
                                  int *blocks) {
     (void)sp;
     if (a.kind == kSweepBinned) return pr_binned_blocks_per_cu(blocks, a.lag != 0);
-    const void *fn = a.kind == kSweepSlots ? slot_sweep_kernel(a, sl.words) : csr_sweep_kernel(a, lanes);
+    const void *fn = a.kind == kSweepSlots   ? slot_sweep_kernel(a, sl.words)
+                     : a.kind == kSweepLists ? list_sweep_kernel(a)
+                                             : csr_sweep_kernel(a, lanes);
     if (!fn) return hipErrorInvalidValue;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, fn, kBlock, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, fn, a.block, 0);
+}
+
+// The buffers of sweep a.sweep of the lagged step, chosen here so that the
+// kernel has their addresses at once.
+static LagBuffers lag_buffers(const PrArgs &a) {
+    const int32_t j = a.sweep;
+    LagBuffers c;
+    c.y_in = a.y[j % 3];
+    c.y_prev = a.y[(j + 2) % 3];
+    c.y_out = a.y[(j + 1) % 3];
+    c.x_in = a.x[j & 1];
+    c.x_out = a.x[(j + 1) & 1];
+    c.part_in = a.partials + (int64_t)((j + 1) & 1) * 3 * a.part_stride;
+    c.part_out = a.partials + (int64_t)(j & 1) * 3 * a.part_stride;
+    return c;
 }
 
 hipError_t launch_pr_sweep_binned(const PrArgs &a, const BinTable &t, int grid, hipStream_t stream) {
     if (t.tiles <= 0) return hipSuccess;
     PrArgs b = a;
+    b.cur = lag_buffers(a);
     b.bins = t;
     void *args[] = {(void *)&b};
-    return hipLaunchKernel(binned_sweep_kernel(a.lag != 0), dim3(grid), dim3(a.lag ? kPanelBlock : kBlock), args, 0,
-                           stream);
+    return hipLaunchKernel(binned_sweep_kernel(a.lag != 0), dim3(grid + (a.lag ? a.reducer : 0)),
+                           dim3(a.lag ? kPanelBlock : kBlock), args, 0, stream);
 }
 
 int32_t bin_panels(const BinTable &t) {
@@ -2633,17 +2910,21 @@ hipError_t launch_bin_rows(const int32_t *row_ptr, int32_t n, const int8_t *clas
 
 hipError_t launch_pr_sweep(const PrArgs &a, const SlotTable &sl, int lanes, int grid, hipStream_t stream) {
     if (a.kind == kSweepBinned) return launch_pr_sweep_binned(a, a.bins, grid, stream);
-    const void *fn = a.kind == kSweepSlots ? slot_sweep_kernel(a, sl.words) : csr_sweep_kernel(a, lanes);
+    const void *fn = a.kind == kSweepSlots   ? slot_sweep_kernel(a, sl.words)
+                     : a.kind == kSweepLists ? list_sweep_kernel(a)
+                                             : csr_sweep_kernel(a, lanes);
     if (!fn) return hipErrorInvalidValue;
-    void *args[] = {(void *)&a};
-    return hipLaunchKernel(fn, dim3(grid), dim3(kBlock), args, 0, stream);
+    PrArgs b = a;
+    b.cur = lag_buffers(a);
+    void *args[] = {(void *)&b};
+    return hipLaunchKernel(fn, dim3(grid + (a.lag ? a.reducer : 0)), dim3(a.block), args, 0, stream);
 }
 
 hipError_t launch_pr_step(const PrArgs &a, int grid, hipStream_t stream) {
     if (a.lag) return hipSuccess;   // the next sweep does the step
     // partial sums: one triple per tile (slot sweep, binned sweep) or per
     // workgroup (CSR sweep)
-    const int32_t count = a.kind == kSweepSlots ? (a.n + kBlock - 1) / kBlock
+    const int32_t count = a.kind == kSweepSlots || a.kind == kSweepLists ? (a.n + kBlock - 1) / kBlock
                           : a.kind == kSweepBinned ? a.bins.tiles : grid;
     hipLaunchKernelGGL(k_pr_finish<false>, dim3(1), dim3(kFinishBlock), 0, stream, a, count);
     return hipGetLastError();
@@ -2655,6 +2936,13 @@ hipError_t launch_pr_iter(const PrArgs &a, const SpaceDesc &sp, const SlotTable 
     hipError_t e = launch_pr_sweep(a, sl, lanes, grid, stream);
     if (e != hipSuccess) return e;
     return launch_pr_step(a, grid, stream);
+}
+
+hipError_t launch_make_lists(const int32_t *row_ptr, const int32_t *col_idx, int32_t n, const WaveLists &wl,
+                             hipStream_t stream) {
+    hipLaunchKernelGGL(k_make_lists, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, stream, row_ptr, col_idx, n,
+                       wl);
+    return hipGetLastError();
 }
 
 hipError_t launch_pr_output(const PrArgs &a, double *pagerank, hipStream_t stream) {

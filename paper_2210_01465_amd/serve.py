@@ -189,7 +189,9 @@ class GpuBackend:
     def plan_bytes(self, plan) -> int:
         s = plan.sizes
         n, n_raw, e = int(s["n_valid"]), int(s["n_raw"]), int(s["n_edges"])
-        return n_raw * 16 + n * (8 * max(int(s["mask_words"]), 1) + 28) + 4 * e
+        # in-edge lists of a small slot space, made when it first runs alone
+        lists = (n + 63) // 64 * 256 * (int(s["n_slots"]) + 32) if s["mask_words"] and e <= 7 << 18 else 0
+        return n_raw * 16 + n * (8 * max(int(s["mask_words"]), 1) + 28) + 4 * e + lists
 
     def member_bytes(self, plan) -> int:
         s = plan.sizes
