@@ -153,6 +153,7 @@ struct fl_ctx {
     std::vector<hipEvent_t> sweep_ev;  // 2 per launch of the longest chunk so far
     BuildSizes *h_sizes = nullptr;  // pinned
     PrState *h_state = nullptr;     // pinned
+    uint64_t *h_progress = nullptr; // pinned: written by the lagged step, polled by the host
     fl_batch *analyze_batch = nullptr;  // kept by fl_analyze_batch between calls (empty between calls)
     // pinned tables of the segmented build (fl_analyze_batch), grown on demand
     fl::SegBuild *h_segs = nullptr;
@@ -1163,11 +1164,13 @@ fl_status fl_create(fl_ctx **out, int device, void *hip_stream) {
         hipDeviceGetAttribute(&ctx->num_cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
         hipHostMalloc((void **)&ctx->h_sizes, sizeof(BuildSizes), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&ctx->h_state, sizeof(PrState), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void **)&ctx->h_progress, 64, hipHostMallocCoherent) != hipSuccess ||
         hipHostMalloc((void **)&ctx->h_bins, sizeof(int32_t) * 64, hipHostMallocDefault) != hipSuccess ||
         scratch_address(device, &ctx->scratch) != hipSuccess) {
         (void)hipGetLastError();
         if (ctx->h_sizes) (void)hipHostFree(ctx->h_sizes);
         if (ctx->h_state) (void)hipHostFree(ctx->h_state);
+        if (ctx->h_progress) (void)hipHostFree(ctx->h_progress);
         if (ctx->h_bins) (void)hipHostFree(ctx->h_bins);
         delete ctx;
         return FL_EHIP;
@@ -1189,6 +1192,7 @@ fl_status fl_destroy(fl_ctx *ctx) {
     for (hipEvent_t e : ctx->sweep_ev) (void)hipEventDestroy(e);
     (void)hipHostFree(ctx->h_sizes);
     (void)hipHostFree(ctx->h_state);
+    (void)hipHostFree(ctx->h_progress);
     (void)hipHostFree(ctx->h_bins);
     delete ctx;
     return FL_OK;
@@ -1242,6 +1246,135 @@ fl_status fl_plan_create(fl_ctx *ctx, const fl_space *space, const float *d_fitn
 
 namespace {
 
+// A pair of events around one sweep (fl_profile): the ctx's j-th pair.
+fl_status sweep_events(fl_ctx *ctx, int j) {
+    while ((int)ctx->sweep_ev.size() < 2 * (j + 1)) {
+        hipEvent_t e;
+        FL_HIP(hipEventCreate(&e));
+        ctx->sweep_ev.push_back(e);
+    }
+    return FL_OK;
+}
+
+// How the lagged sweeps' host loop stands: what the device last reported.
+struct Progress {
+    int32_t sweep = 0;    // the step of sweep - 1 is done
+    bool stopped = false;
+    double resid = 0.0;
+};
+Progress read_progress(const uint64_t *word) {
+    const uint64_t w = __atomic_load_n(word, __ATOMIC_ACQUIRE);
+    Progress p;
+    p.sweep = (int32_t)((w >> 32) & 0x7fffffffu);
+    p.stopped = (w >> 63) & 1;
+    float r;
+    const uint32_t lo = (uint32_t)w;
+    memcpy(&r, &lo, 4);
+    p.resid = (double)r;
+    return p;
+}
+
+// The sweeps of the lagged step.  Every sweep's step reports to a pinned host
+// word, and the host keeps a few launches ahead of it (a launch after the stop
+// exits at once) instead of copying the state back and waiting for the stream
+// once per chunk of sweeps, which left the device idle for about 25 us each
+// time.  Near the sweep that should stop, by the residual's decay, it keeps
+// fewer ahead.  With the step one sweep late (and the
+// power iteration's residual another), the sweep after the cap's last
+// iteration does only that step and stops.
+constexpr int kSweepLead = 6;      // launches ahead of the last report: a launch takes the host about 3 us,
+                                   // the shortest sweep 3, a report 1 to 2
+constexpr int kLastLead = 2;       // near the end
+fl_status run_lagged(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int lanes, int grid, bool exact,
+                     int32_t profile_every, int *launches_out) {
+    hipStream_t s = ctx->stream;
+    const int64_t limit = (int64_t)r.max_iter + (exact ? 1 : 2);
+    __atomic_store_n(ctx->h_progress, uint64_t(0), __ATOMIC_RELEASE);
+    a.progress = ctx->h_progress;
+    int64_t launches = 0, ahead = kSweepLead;
+    Progress seen;
+    uint32_t idle = 0;
+    for (;;) {
+        const bool room = launches < std::min(limit, seen.sweep + ahead);
+        if (room) {
+            a.sweep = (int32_t)launches;
+            const bool timed_here = profile_every > 0 && launches % profile_every == 0;
+            const int pair = timed_here ? (int)(launches / profile_every) : 0;
+            if (timed_here) {
+                const fl_status st = sweep_events(ctx, pair);
+                if (st != FL_OK) return st;
+                FL_HIP(hipEventRecord(ctx->sweep_ev[2 * pair], s));
+            }
+            FL_HIP(fl::launch_pr_sweep(a, p->sl, lanes, grid, s));
+            if (timed_here) FL_HIP(hipEventRecord(ctx->sweep_ev[2 * pair + 1], s));
+            ++launches;
+        }
+        const Progress now = read_progress(ctx->h_progress);
+        if (now.stopped) break;
+        if (now.sweep > seen.sweep) {
+            // sweeps until the residual falls below the tolerance at the rate
+            // seen between two reports (the exact method has no such decay)
+            if (!exact && seen.sweep >= 2 && now.resid > r.tol && seen.resid > now.resid) {
+                const double rate = log(now.resid / seen.resid) / (now.sweep - seen.sweep);
+                const double more = ceil(log(r.tol / now.resid) / rate);
+                ahead = (int64_t)std::min<double>(std::max<double>(more + 1.0, kLastLead), kSweepLead);
+            }
+            seen = now;
+            idle = 0;
+        } else if (++idle % 4096 == 0) {
+            // nothing new for a while: an error, or the stream has drained
+            const hipError_t q = hipStreamQuery(s);
+            if (q == hipErrorNotReady) (void)hipGetLastError();
+            if (q != hipSuccess && q != hipErrorNotReady) FL_HIP(q);
+            if (q == hipSuccess && launches >= limit && !read_progress(ctx->h_progress).stopped)
+                return fail(ctx, FL_EHIP, "the iteration did not stop after %lld sweeps", (long long)launches);
+        } else if (!room) {
+            __builtin_ia32_pause();
+        }
+    }
+    *launches_out = (int)launches;
+    return FL_OK;
+}
+
+// The sweeps with a step kernel after each (FL_STEP_SEPARATE), in chunks: the
+// chunk length follows the observed residual decay so that few host round
+// trips and few empty launches are needed.
+fl_status run_separate(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int lanes, int grid, bool exact,
+                       int32_t profile_every, int *launches_out) {
+    hipStream_t s = ctx->stream;
+    PrState *hs = ctx->h_state;
+    int launches = 0, chunk = 16;
+    for (;;) {
+        for (int j = 0; j < chunk; ++j, ++launches) {
+            const bool timed_here = profile_every > 0 && launches % profile_every == 0;
+            const int pair = timed_here ? launches / profile_every : 0;
+            if (timed_here) {
+                const fl_status st = sweep_events(ctx, pair);
+                if (st != FL_OK) return st;
+                FL_HIP(hipEventRecord(ctx->sweep_ev[2 * pair], s));
+            }
+            FL_HIP(fl::launch_pr_sweep(a, p->sl, lanes, grid, s));
+            if (timed_here) FL_HIP(hipEventRecord(ctx->sweep_ev[2 * pair + 1], s));
+            FL_HIP(fl::launch_pr_step(a, grid, s));
+        }
+        FL_HIP(hipMemcpyAsync(hs, p->state, sizeof(PrState), hipMemcpyDeviceToHost, s));
+        FL_HIP(hipStreamSynchronize(s));
+        if (hs->done) break;
+        const double rate = (hs->resid_prev > 0.0) ? hs->resid / hs->resid_prev : 1.0;
+        if (exact) {
+            chunk = 64;   // the sweeps end abruptly (exact fixed point): no decay to follow
+        } else if (rate > 0.0 && rate < 0.999 && hs->resid > r.tol) {
+            const double more = ceil(log(r.tol / hs->resid) / log(rate));
+            chunk = (int)std::min(64.0, std::max(2.0, more + 1.0));
+        } else {
+            chunk = 8;
+        }
+        chunk = std::min(chunk, std::max(1, r.max_iter - hs->k));
+    }
+    *launches_out = launches;
+    return FL_OK;
+}
+
 // PageRank, minima and C_p of a built plan.  quiet: no timing events are
 // created or recorded and no sweep is profiled (fl_analyze_noalloc).
 fl_status execute_impl(fl_ctx *ctx, fl_plan *p, const fl_params *prm, double *d_pagerank, int32_t *d_minima,
@@ -1270,77 +1403,30 @@ fl_status execute_impl(fl_ctx *ctx, fl_plan *p, const fl_params *prm, double *d_
     if (timed) FL_HIP(ensure_events(p));
 
     if (timed) FL_HIP(hipEventRecord(p->ev[2], s));
-    FL_HIP(hipMemsetAsync(p->state, 0, sizeof(PrState), s));
+    if (!r.lag) FL_HIP(hipMemsetAsync(p->state, 0, sizeof(PrState), s));   // the lagged start writes it whole
     FL_HIP(fl::launch_pr_init(a, init_grid, s));
-
-    // Launch the iteration kernel in chunks; a launch after convergence exits
-    // at once.  The chunk length follows the observed residual decay so that
-    // few host round trips and few empty launches are needed.  With the
-    // lagged step the sweeps alone are launched, and the step of iteration k
-    // runs in sweep k + 1 (k + 2 for the power iteration, whose residual is
-    // one sweep late as well): the sweep after the cap's last iteration does
-    // only that step, and sets the stop flag.
+    if (timed) FL_HIP(hipEventRecord(p->ev[5], s));
     int launches = 0;
-    int chunk = 16;
-    const int64_t limit = r.lag ? (int64_t)r.max_iter + (exact ? 1 : 2) : INT64_MAX;
-    double iterate_ms = 0.0, sweep_ms = 0.0;
-    PrState *hs = ctx->h_state;
-    int sampled = 0;
-    for (;;) {
-        if (profile_every > 0 && (int)ctx->sweep_ev.size() < 2 * chunk) {
-            for (int j = (int)ctx->sweep_ev.size(); j < 2 * chunk; ++j) {
-                hipEvent_t e;
-                FL_HIP(hipEventCreate(&e));
-                ctx->sweep_ev.push_back(e);
-            }
-        }
-        if (timed) FL_HIP(hipEventRecord(p->ev[5], s));
-        for (int j = 0; j < chunk; ++j) {
-            const bool sampled_here = profile_every > 0 && (launches + j) % profile_every == 0;
-            a.sweep = launches + j;
-            if (sampled_here) FL_HIP(hipEventRecord(ctx->sweep_ev[2 * j], s));
-            FL_HIP(fl::launch_pr_sweep(a, p->sl, lanes, grid, s));
-            if (sampled_here) FL_HIP(hipEventRecord(ctx->sweep_ev[2 * j + 1], s));
-            FL_HIP(fl::launch_pr_step(a, grid, s));
-        }
-        if (timed) FL_HIP(hipEventRecord(p->ev[6], s));
-        const int before = launches;
-        launches += chunk;
-        FL_HIP(hipMemcpyAsync(hs, p->state, sizeof(PrState), hipMemcpyDeviceToHost, s));
-        FL_HIP(hipStreamSynchronize(s));
-        if (timed) iterate_ms += elapsed(p->ev[5], p->ev[6]);
-        if (profile_every > 0)   // launches past the converged iteration exit at once: not counted
-            for (int j = 0; j < chunk && before + j < hs->worked; ++j)
-                if ((before + j) % profile_every == 0) {
-                    sweep_ms += elapsed(ctx->sweep_ev[2 * j], ctx->sweep_ev[2 * j + 1]);
-                    ++sampled;
-                }
-        if (hs->done) break;
-        if (launches >= limit) return fail(ctx, FL_EHIP, "the iteration did not stop after %d sweeps", launches);
-        const double rate = (hs->resid_prev > 0.0) ? hs->resid / hs->resid_prev : 1.0;
-        if (exact) {
-            chunk = 64;   // the sweeps end abruptly (exact fixed point): no decay to follow
-        } else if (rate > 0.0 && rate < 0.999 && hs->resid > r.tol) {
-            const double more = ceil(log(r.tol / hs->resid) / log(rate));
-            chunk = (int)std::min(64.0, std::max(2.0, more + 1.0));
-        } else {
-            chunk = 8;
-        }
-        chunk = std::min(chunk, std::max(1, r.max_iter - hs->k));
-        if (r.lag) chunk = (int)std::min<int64_t>(chunk, limit - launches);
-    }
+    st = (r.lag ? run_lagged : run_separate)(ctx, p, r, a, lanes, grid, exact, profile_every, &launches);
+    if (st != FL_OK) return st;
+    if (timed) FL_HIP(hipEventRecord(p->ev[6], s));
     if (timed) FL_HIP(hipEventRecord(p->ev[3], s));
-    FL_HIP(fl::launch_pr_output(a, d_pagerank, s));
-    if (p->m > 0) FL_HIP(hipMemcpyAsync(d_minima, p->minima, sizeof(int32_t) * p->m, hipMemcpyDeviceToDevice, s));
+    FL_HIP(fl::launch_pr_output(a, d_pagerank, p->minima, (int32_t)p->m, d_minima, s));
     const double threshold = (1.0 + r.p) * (double)p->f_opt;
     FL_HIP(fl::launch_score(d_pagerank, p->minima, (int32_t)p->m, p->fit_c, threshold, p->state, s));
     if (timed) FL_HIP(hipEventRecord(p->ev[4], s));
+    PrState *hs = ctx->h_state;
     FL_HIP(hipMemcpyAsync(hs, p->state, sizeof(PrState), hipMemcpyDeviceToHost, s));
     FL_HIP(hipStreamSynchronize(s));
 
+    double sweep_ms = 0.0;
+    int sampled = 0;
+    if (profile_every > 0)   // launches past the converged iteration exit at once: not counted
+        for (int j = 0; j < launches && j < hs->worked; j += profile_every, ++sampled)
+            sweep_ms += elapsed(ctx->sweep_ev[2 * sampled], ctx->sweep_ev[2 * sampled + 1]);
     p->timing.pagerank_ms = timed ? elapsed(p->ev[2], p->ev[3]) : 0.0;
     p->timing.score_ms = timed ? elapsed(p->ev[3], p->ev[4]) : 0.0;
-    p->timing.iterate_ms = iterate_ms;
+    p->timing.iterate_ms = timed ? elapsed(p->ev[5], p->ev[6]) : 0.0;
     p->timing.sweep_ms = sweep_ms;
     p->timing.sweeps_timed = sampled;
     p->timing.iterations = hs->worked;

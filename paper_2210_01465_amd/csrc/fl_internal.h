@@ -244,6 +244,7 @@ struct PrArgs {
     int32_t block;     // threads per workgroup of the sweep (list sweep: 64 or kBlock; else kBlock)
     int32_t reducer;   // 1: the step has a workgroup of its own (the first of grid + 1)
     int64_t n_sinks;
+    uint64_t *progress;   // pinned host word the step reports to (may be null)
     float *g;
 };
 
@@ -316,7 +317,8 @@ hipError_t pr_iter_blocks_per_cu(const PrArgs &a, const SpaceDesc &sp, const Slo
                                  int *blocks);
 hipError_t launch_make_lists(const int32_t *row_ptr, const int32_t *col_idx, int32_t n, const WaveLists &wl,
                              hipStream_t stream);
-hipError_t launch_pr_output(const PrArgs &a, double *pagerank, hipStream_t stream);
+hipError_t launch_pr_output(const PrArgs &a, double *pagerank, const int32_t *minima, int32_t m, int32_t *out_minima,
+                            hipStream_t stream);
 // Binning of the rows by in-degree class: class_of[b] is the class of bucket
 // b.  Count per (class, node tile) into cnt (kBuckets x n_tiles, class-major),
 // scan it into off and totals (kBuckets entries), write bin_rows.

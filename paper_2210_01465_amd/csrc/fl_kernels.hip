@@ -1233,6 +1233,16 @@ __device__ __forceinline__ int32_t peek_stop(const PrState *st) {
 }
 __device__ __forceinline__ bool stop_seen(int32_t peeked) { return __builtin_amdgcn_readfirstlane(peeked) != 0; }
 
+// Tells the host how far the iteration is: sweep j has done the step of
+// sweep j - 1 (bits 32..62), whether it stopped (bit 63), and the last
+// residual (FP32).  One 8-byte store to pinned host memory.
+__device__ __forceinline__ void tell_host(const PrArgs &a, int32_t stop, double resid) {
+    if (!a.progress) return;
+    const uint64_t word = ((uint64_t)(uint32_t)a.sweep | (stop ? 1ull << 31 : 0ull)) << 32 |
+                          __float_as_uint((float)resid);
+    __hip_atomic_store(a.progress, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Workgroup 0 of sweep j >= 1: reduce the partial triples of sweep j - 1
 // in a fixed order (thread t sums parts t, t + B, ...; then a fixed
 // tree) and do its step.  Sweep j - 1 wrote sum w_j, the residual
@@ -1283,8 +1293,10 @@ __device__ void lag_step(const PrArgs &a) {
             st->out_sigma = r0;
             set_stop(st, stop);
         }
+        tell_host(a, stop, r1);
         return;
     }
+    int32_t stop = 0;
     const double ga = st->gam[j & 1][0], gb = st->gam[j & 1][1];   // gamma_{j-1}, gamma_{j-2}
     const double n = (double)a.n;
     const double sig = r0 + n * ga;                        // sum of r_j
@@ -1294,7 +1306,7 @@ __device__ void lag_step(const PrArgs &a) {
         st->resid = r1;
         st->k = j - 1;
         st->worked = j - 1;
-        const int32_t stop = r1 < a.tol ? 1 : (j - 1 >= a.max_iter ? 2 : 0);
+        stop = r1 < a.tol ? 1 : (j - 1 >= a.max_iter ? 2 : 0);
         if (stop) {
             // r_{j-1} = w_{j-1} + gamma_{j-2}, summed by the previous step
             st->out_buf = (j - 1) % 3;
@@ -1303,6 +1315,7 @@ __device__ void lag_step(const PrArgs &a) {
             set_stop(st, stop);
         }
     }
+    tell_host(a, stop, j >= 2 ? r1 : 0.0);
     const double gj = (a.d * sink + (1.0 - a.d)) / n;   // gamma_j
     st->gam[(j + 1) & 1][0] = gj;
     st->gam[(j + 1) & 1][1] = ga;
@@ -1451,6 +1464,7 @@ __global__ __launch_bounds__(kBlock) void k_pr_init_lag(PrArgs a) {
         st->out_buf = 0;
         st->out_gamma = 0.0;
         st->out_sigma = s0;
+        st->score_num = st->score_den = 0.0;
     }
 }
 
@@ -2555,8 +2569,12 @@ __global__ void k_batch_states(const BatchMember *__restrict__ members, const in
     if (j < n_members) states_out[j] = *members[member_ids[j]].st;
 }
 
-__global__ __launch_bounds__(kBlock) void k_pr_output(PrArgs a, double *__restrict__ pagerank) {
+// Ranks scaled to sum 1, and the minima, into the caller's buffers.
+__global__ __launch_bounds__(kBlock) void k_pr_output(PrArgs a, double *__restrict__ pagerank,
+                                                      const int32_t *__restrict__ minima, int32_t m,
+                                                      int32_t *__restrict__ out_minima) {
     const PrState *st = a.st;
+    for (int32_t j = blockIdx.x * kBlock + threadIdx.x; j < m; j += gridDim.x * kBlock) out_minima[j] = minima[j];
     if (a.lag) {
         // r = w + gamma, scaled to sum 1
         const float *__restrict__ y = a.y[st->out_buf];
@@ -2945,9 +2963,10 @@ hipError_t launch_make_lists(const int32_t *row_ptr, const int32_t *col_idx, int
     return hipGetLastError();
 }
 
-hipError_t launch_pr_output(const PrArgs &a, double *pagerank, hipStream_t stream) {
+hipError_t launch_pr_output(const PrArgs &a, double *pagerank, const int32_t *minima, int32_t m, int32_t *out_minima,
+                            hipStream_t stream) {
     const int grid = (int)(((int64_t)a.n + kBlock - 1) / kBlock < 4096 ? ((int64_t)a.n + kBlock - 1) / kBlock : 4096);
-    hipLaunchKernelGGL(k_pr_output, dim3(grid), dim3(kBlock), 0, stream, a, pagerank);
+    hipLaunchKernelGGL(k_pr_output, dim3(grid), dim3(kBlock), 0, stream, a, pagerank, minima, m, out_minima);
     return hipGetLastError();
 }
 
