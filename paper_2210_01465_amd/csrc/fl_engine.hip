@@ -151,7 +151,8 @@ struct fl_ctx {
     int32_t *h_bins = nullptr;      // pinned: bucket classes out, class sizes back
     int32_t profile_every = 0;      // bracket every n-th sweep kernel with events (fl_profile), 0 = off
     std::vector<hipEvent_t> sweep_ev;  // 2 per launch of the longest chunk so far
-    BuildSizes *h_sizes = nullptr;  // pinned
+    BuildSizes *h_sizes = nullptr;  // pinned: written by the build stages, polled by the host
+    uint32_t stamp = 0;             // of the last build stage that reports to h_sizes
     PrState *h_state = nullptr;     // pinned
     uint64_t *h_progress = nullptr; // pinned: written by the lagged step, polled by the host
     fl_batch *analyze_batch = nullptr;  // kept by fl_analyze_batch between calls (empty between calls)
@@ -183,6 +184,7 @@ struct fl_plan {
     uint64_t *rec = nullptr;    // node records (in-edge slot bits, out_deg, raw index)
     uint64_t *presence = nullptr;  // per wave of 64 nodes: OR of their slot bits
     fl::SlotTable sl{};
+    bool has_csr = true;        // false for a plan that runs once and by slots: no row_ptr, col_idx
     fl::WaveLists lists{};      // in-edge lists of a small slot space, made by its first execute
     // power-iteration working set, allocated by the first fl_execute
     float *y[3] = {nullptr, nullptr, nullptr};   // the third for the lagged step
@@ -388,6 +390,78 @@ float elapsed(hipEvent_t a, hipEvent_t b) {
 }
 
 
+// Bytes the slot sweep's buffer loads span: its descriptor starts at the most
+// negative slot offset below x, and the loads reach the end of x plus the
+// largest offset; 0 when that does not fit a signed 32-bit offset (the
+// sweep then uses plain loads).
+int32_t x_bytes_of(const fl_plan *p) {
+    if (p->sl.k <= 0) return 0;
+    const int64_t span = (p->n_raw + 3) / 4 * 4 + (int64_t)p->sl.off[p->sl.k - 1] - (int64_t)p->sl.off[0];
+    const int64_t b = 4 * span + 64;
+    return b < (int64_t(1) << 31) ? (int32_t)b : 0;
+}
+
+bool is_slot_layout(int lanes) { return lanes == FL_ROWS_SLOTS; }
+bool is_binned_layout(int lanes) { return lanes == FL_ROWS_BINNED; }
+
+// Shape class of a plan for the tuning cache: record width, neighbourhood,
+// log2 N and the mean in-degree rounded to a half.
+uint64_t shape_key(const fl_plan *p) {
+    int lg = 0;
+    while ((int64_t(1) << (lg + 1)) <= p->n) ++lg;
+    const int64_t deg2 = p->n > 0 ? (2 * p->e + p->n / 2) / p->n : 0;
+    return ((uint64_t)p->sl.words << 56) | ((uint64_t)p->adjacent << 52) | ((uint64_t)lg << 40) |
+           (uint64_t)std::min<int64_t>(deg2, (int64_t(1) << 40) - 1);
+}
+
+// Layout a plan runs in: the one asked for, else the one tuned for its shape
+// class, else the default.
+int layout_of(const fl_ctx *ctx, const fl_plan *p, const fl_params *prm) {
+    if (prm->row_mapping != 0) return prm->row_mapping;
+    const auto hit = ctx->tuned.find(shape_key(p));
+    if (hit != ctx->tuned.end()) return hit->second;
+    return p->sl.words > 0 ? FL_ROWS_SLOTS : FL_ROWS_BINNED;
+}
+
+// Whether a plan runs by bins as a batch member (explicit or automatic layout).
+// A tuned lanes-per-row CSR layout wins on a lone space by spreading it over
+// more workgroups; in a batch the members supply that parallelism, so such
+// members keep the slot sweep.
+bool member_binned(const fl_ctx *ctx, const fl_plan *p, const fl_params *prm) {
+    if (is_slot_layout(prm->row_mapping)) return false;
+    if (is_binned_layout(prm->row_mapping)) return true;
+    const auto hit = ctx->tuned.find(shape_key(p));
+    return !(p->sl.words > 0 && x_bytes_of(p) > 0) || (hit != ctx->tuned.end() && hit->second == FL_ROWS_BINNED);
+}
+
+// Quads per wave of a plan's in-edge lists: a node has at most as many
+// in-edges as neighbours; one group more, so that whole groups can be read.
+int64_t list_stride(const fl_plan *p) {
+    const int64_t most = p->adjacent ? p->sl.k : p->sl.k / 2;
+    return std::max<int64_t>((most + 3) / 4, fl::kListQuads) + fl::kListQuads;
+}
+int64_t list_bytes(const fl_plan *p) { return (p->n + 63) / 64 * (list_stride(p) * 64 * (int64_t)sizeof(uint4) + 4); }
+
+// Whether a slot space is swept by lists: few edges (kListEdges), and lists
+// that fit the scratch array of fl_analyze_noalloc beside everything else the
+// analysis keeps there, so that it takes the same path as fl_analyze.
+bool wants_lists(const fl_plan *p) {
+    if (p->sl.words == 0 || p->e > fl::kListEdges) return false;
+    const int64_t rest = 20 * p->n_raw + (40 + 8 * (int64_t)p->sl.words) * p->n + 4 * p->e + (int64_t(1) << 20);
+    return rest + list_bytes(p) <= (int64_t)kNoAllocScratchBytes;
+}
+
+// Room for the lists; false when it cannot be had.
+bool alloc_lists(fl_ctx *ctx, fl_plan *p) {
+    const int64_t waves = (p->n + 63) / 64, stride = list_stride(p);
+    char *block = pool_alloc<char>(ctx, list_bytes(p));
+    if (!block) return false;
+    p->lists.quad = reinterpret_cast<uint4 *>(block);
+    p->lists.quads = reinterpret_cast<int32_t *>(p->lists.quad + waves * stride * 64);
+    p->lists.stride = (int32_t)stride;
+    return true;
+}
+
 // ---------------------------------------------------------------------------
 // Plan building in resumable stages, so that many spaces can be built with one
 // host synchronisation per stage (fl_analyze_batch) as well as one at a time.
@@ -404,6 +478,9 @@ struct Build {
                                     // compaction only, the generic kernels still launch here)
     BuildSizes *h_sizes = nullptr;  // pinned slot for this build's sizes
     fl_plan *storage = nullptr;     // caller-owned plan object to build into (else one is allocated)
+    const fl_params *once = nullptr;  // the plan runs once, with these parameters, and is then destroyed:
+                                      // only what that run reads is built
+    bool slots_only = false;        // (once) swept by slot records or lists: no CSR
     const float *fit = nullptr;
     int32_t *remap = nullptr, *tile_cnt = nullptr, *tile_bad = nullptr, *tile_off = nullptr;
     float *tile_min = nullptr;
@@ -454,6 +531,29 @@ void build_abort(fl_ctx *ctx, Build &b) {
             for (auto &e : b.p->ev) (void)hipEventDestroy(e);
         if (b.p != b.storage) delete b.p;
         b.p = nullptr;
+    }
+}
+
+// Where the next stage of a single build reports its sizes (a build of many
+// spaces copies them all at once instead).
+fl::HostSizes next_stamp(fl_ctx *ctx, const Build &b) {
+    if (b.shared_sizes) return {nullptr, 0};
+    return {b.h_sizes, ++ctx->stamp};
+}
+
+// Waits until the stage launched last has reported its sizes.
+void build_wait(fl_ctx *ctx, Build &b) {
+    if (b.status != FL_OK) return;
+    for (uint32_t spins = 1; __atomic_load_n(&b.h_sizes->stamp, __ATOMIC_ACQUIRE) != ctx->stamp; ++spins) {
+        __builtin_ia32_pause();
+        if (spins % 4096 != 0) continue;
+        const hipError_t q = hipStreamQuery(ctx->stream);
+        if (q == hipErrorNotReady) {
+            (void)hipGetLastError();
+            continue;
+        }
+        if (q == hipSuccess && __atomic_load_n(&b.h_sizes->stamp, __ATOMIC_ACQUIRE) == ctx->stamp) return;
+        return build_fail(b, FL_EHIP, "build stage: %s", q == hipSuccess ? "no sizes reported" : hipGetErrorString(q));
     }
 }
 
@@ -511,9 +611,7 @@ void build_begin(fl_ctx *ctx, Build &b, const fl_space *space, const float *fit,
     hipError_t he = b.timed ? hipEventRecord(p->ev[0], s) : hipSuccess;
     if (he == hipSuccess && !b.defer)
         he = fl::launch_compact_single(fit, sp.n_raw, b.tile_cnt, b.tile_min, b.tile_bad, b.remap, p->valid_raw,
-                                       p->fit_c, b.d_sizes, s);
-    if (he == hipSuccess && !b.shared_sizes)
-        he = hipMemcpyAsync(b.h_sizes, b.d_sizes, sizeof(BuildSizes), hipMemcpyDeviceToHost, s);
+                                       p->fit_c, b.d_sizes, next_stamp(ctx, b), s);
     if (he != hipSuccess) build_fail(b, FL_EHIP, "compaction: %s", hipGetErrorString(he));
 }
 
@@ -546,14 +644,15 @@ void build_degree(fl_ctx *ctx, Build &b) {
     if (b.defer && p->sl.words > 0) return;
     hipError_t he = fl::launch_degree(p->sp, p->sl, p->adjacent, b.fit, p->valid_raw, n, b.in_deg, p->out_deg,
                                       p->rec, p->presence, p->d_off, k_pad_of(p->sl), b.tile_e, b.tile_m,
-                                      b.tile_eoff, b.tile_moff, b.d_sizes, s);
-    if (he == hipSuccess && !b.shared_sizes)
-        he = hipMemcpyAsync(b.h_sizes, b.d_sizes, sizeof(BuildSizes), hipMemcpyDeviceToHost, s);
+                                      b.tile_eoff, b.tile_moff, b.d_sizes, next_stamp(ctx, b), s);
     if (he != hipSuccess) build_fail(b, FL_EHIP, "degree count: %s", hipGetErrorString(he));
 }
 
 // Stage 3 (edge count on the host): CSR fill and minima (Sec. III-B, VII-B).
-void build_fill(fl_ctx *ctx, Build &b) {
+// A plan that runs once by slot records gets its minima alone, one that runs
+// once by lists gets those from its records (`alone`: by execute_impl, else as
+// a batch member, which has no lists).
+void build_fill(fl_ctx *ctx, Build &b, bool alone = true) {
     if (b.status != FL_OK) return;
     fl_plan *p = b.p;
     const int64_t e = b.h_sizes->n_edges;
@@ -561,13 +660,26 @@ void build_fill(fl_ctx *ctx, Build &b) {
     p->e = e;
     p->m = b.h_sizes->n_minima;
     p->n_plateau = b.h_sizes->n_plateau;
-    p->col_idx = pool_alloc<int32_t>(ctx, e);
-    if (!p->col_idx) return build_fail(b, FL_ENOMEM, "device allocation failed");
+    b.slots_only = b.once && p->sl.words > 0 &&
+                   (alone ? is_slot_layout(layout_of(ctx, p, b.once)) : !member_binned(ctx, p, b.once) && b.once->row_mapping <= 0);
+    p->has_csr = !b.slots_only;
+    // the scratch array accounts for the CSR either way, so that it takes the
+    // same spaces
+    if (!b.slots_only || ctx->arena) {
+        p->col_idx = pool_alloc<int32_t>(ctx, e);
+        if (!p->col_idx) return build_fail(b, FL_ENOMEM, "device allocation failed");
+    }
     hipStream_t s = ctx->stream;
     if (b.defer && p->sl.words > 0) return;
-    hipError_t he = fl::launch_fill(p->sp, p->sl, p->adjacent, b.fit, p->valid_raw, b.remap, p->rec, p->presence,
-                                    (int32_t)p->n, (int32_t)e, b.in_deg, p->out_deg, b.tile_eoff, b.tile_moff,
-                                    p->row_ptr, p->col_idx, p->minima, s);
+    const bool lists = b.slots_only && wants_lists(p);
+    hipError_t he = hipSuccess;
+    if (lists && !alloc_lists(ctx, p)) return build_fail(b, FL_ENOMEM, "device allocation failed");
+    if (b.slots_only && !lists)
+        he = fl::launch_fill_minima(p->out_deg, (int32_t)p->n, b.tile_moff, p->minima, s);
+    else
+        he = fl::launch_fill(p->sp, p->sl, p->adjacent, b.fit, p->valid_raw, b.remap, p->rec, p->presence,
+                             (int32_t)p->n, (int32_t)e, b.in_deg, p->out_deg, b.tile_eoff, b.tile_moff, p->row_ptr,
+                             p->col_idx, p->minima, lists ? &p->lists : nullptr, s);
     if (he == hipSuccess && b.timed) he = hipEventRecord(p->ev[1], s);
     if (he != hipSuccess) build_fail(b, FL_EHIP, "CSR fill: %s", hipGetErrorString(he));
 }
@@ -592,20 +704,6 @@ void fill_sizes(const fl_plan *p, fl_summary *sizes) {
 }
 
 // Analysis parameters with the defaults applied.
-// Bytes the slot sweep's buffer loads span: its descriptor starts at the most
-// negative slot offset below x, and the loads reach the end of x plus the
-// largest offset; 0 when that does not fit a signed 32-bit offset (the
-// sweep then uses plain loads).
-int32_t x_bytes_of(const fl_plan *p) {
-    if (p->sl.k <= 0) return 0;
-    const int64_t span = (p->n_raw + 3) / 4 * 4 + (int64_t)p->sl.off[p->sl.k - 1] - (int64_t)p->sl.off[0];
-    const int64_t b = 4 * span + 64;
-    return b < (int64_t(1) << 31) ? (int32_t)b : 0;
-}
-
-bool is_slot_layout(int lanes) { return lanes == FL_ROWS_SLOTS; }
-bool is_binned_layout(int lanes) { return lanes == FL_ROWS_BINNED; }
-
 // ---- rows binned by in-degree ----
 // A bucket mapping: byte b holds log2 of bucket b's lanes per row (bits 0..2)
 // and of its row blocks per tile (bits 3..4).
@@ -753,32 +851,10 @@ fl_status resolve_params(fl_ctx *ctx, const fl_plan *p, const fl_params *prm, Re
     return FL_OK;
 }
 
-// Quads per wave of a plan's in-edge lists: a node has at most as many
-// in-edges as neighbours; one group more, so that whole groups can be read.
-int64_t list_stride(const fl_plan *p) {
-    const int64_t most = p->adjacent ? p->sl.k : p->sl.k / 2;
-    return std::max<int64_t>((most + 3) / 4, fl::kListQuads) + fl::kListQuads;
-}
-int64_t list_bytes(const fl_plan *p) { return (p->n + 63) / 64 * (list_stride(p) * 64 * (int64_t)sizeof(uint4) + 4); }
-
-// Whether a slot space is swept by lists: few edges (kListEdges), and lists
-// that fit the scratch array of fl_analyze_noalloc beside everything else the
-// analysis keeps there, so that it takes the same path as fl_analyze.
-bool wants_lists(const fl_plan *p) {
-    if (p->sl.words == 0 || p->e > fl::kListEdges) return false;
-    const int64_t rest = 20 * p->n_raw + (40 + 8 * (int64_t)p->sl.words) * p->n + 4 * p->e + (int64_t(1) << 20);
-    return rest + list_bytes(p) <= (int64_t)kNoAllocScratchBytes;
-}
-
-// The lists of such a plan, made by its first execute and kept with it.
+// The lists of a kept plan, made from its CSR by its first execute.
 fl_status ensure_lists(fl_ctx *ctx, fl_plan *p) {
     if (p->lists.quad) return FL_OK;
-    const int64_t waves = (p->n + 63) / 64, stride = list_stride(p);
-    char *block = pool_alloc<char>(ctx, list_bytes(p));
-    if (!block) return fail(ctx, FL_ENOMEM, "device allocation failed");
-    p->lists.quad = reinterpret_cast<uint4 *>(block);
-    p->lists.quads = reinterpret_cast<int32_t *>(p->lists.quad + waves * stride * 64);
-    p->lists.stride = (int32_t)stride;
+    if (!alloc_lists(ctx, p)) return fail(ctx, FL_ENOMEM, "device allocation failed");
     FL_HIP(fl::launch_make_lists(p->row_ptr, p->col_idx, (int32_t)p->n, p->lists, ctx->stream));
     return FL_OK;
 }
@@ -837,16 +913,6 @@ void fill_summary(const fl_plan *p, const PrState &hs, int lanes, fl_status stat
     out->score = hs.score_den > 0.0 ? hs.score_num / hs.score_den : 0.0;
 }
 
-// Shape class of a plan for the tuning cache: record width, neighbourhood,
-// log2 N and the mean in-degree rounded to a half.
-uint64_t shape_key(const fl_plan *p) {
-    int lg = 0;
-    while ((int64_t(1) << (lg + 1)) <= p->n) ++lg;
-    const int64_t deg2 = p->n > 0 ? (2 * p->e + p->n / 2) / p->n : 0;
-    return ((uint64_t)p->sl.words << 56) | ((uint64_t)p->adjacent << 52) | ((uint64_t)lg << 40) |
-           (uint64_t)std::min<int64_t>(deg2, (int64_t(1) << 40) - 1);
-}
-
 uint64_t bin_map_for(const fl_ctx *ctx, uint64_t shape) {
     const auto it = ctx->tuned_map.find(shape);
     return it != ctx->tuned_map.end() ? it->second : default_bin_map();
@@ -858,6 +924,8 @@ fl_status prepare_pr(fl_ctx *ctx, fl_plan *p, const Resolved &r, int lanes, PrAr
                      int &init_grid) {
     int kind = is_slot_layout(lanes) ? fl::kSweepSlots : is_binned_layout(lanes) ? fl::kSweepBinned
                                                                                 : fl::kSweepCsr;
+    if (kind != fl::kSweepSlots && !p->has_csr) return fail(ctx, FL_EINVAL, "the plan was built for the slot layout");
+    fl_status st = FL_OK;
     a = PrArgs{};
     a.kind = kind;
     a.block = fl::kBlock;
@@ -868,9 +936,9 @@ fl_status prepare_pr(fl_ctx *ctx, fl_plan *p, const Resolved &r, int lanes, PrAr
         a.bin_rows = p->bin_rows;
         a.bins = p->bins;
     }
-    fl_status st = ensure_pr_buffers(ctx, p, kind == fl::kSweepSlots, r.lag);
+    st = ensure_pr_buffers(ctx, p, kind == fl::kSweepSlots, r.lag);
     if (st != FL_OK) return st;
-    if (kind == fl::kSweepSlots && wants_lists(p)) {
+    if (kind == fl::kSweepSlots && wants_lists(p) && (p->has_csr || p->lists.quad)) {
         st = ensure_lists(ctx, p);
         if (st != FL_OK) return st;
         kind = a.kind = fl::kSweepLists;
@@ -1162,7 +1230,7 @@ fl_status fl_create(fl_ctx **out, int device, void *hip_stream) {
     ctx->stream = static_cast<hipStream_t>(hip_stream);
     if (hipSetDevice(device) != hipSuccess ||
         hipDeviceGetAttribute(&ctx->num_cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
-        hipHostMalloc((void **)&ctx->h_sizes, sizeof(BuildSizes), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void **)&ctx->h_sizes, sizeof(BuildSizes), hipHostMallocCoherent) != hipSuccess ||
         hipHostMalloc((void **)&ctx->h_state, sizeof(PrState), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&ctx->h_progress, 64, hipHostMallocCoherent) != hipSuccess ||
         hipHostMalloc((void **)&ctx->h_bins, sizeof(int32_t) * 64, hipHostMallocDefault) != hipSuccess ||
@@ -1212,17 +1280,13 @@ fl_status fl_plan_create(fl_ctx *ctx, const fl_space *space, const float *d_fitn
     FL_HIP(hipSetDevice(ctx->device));
     Build b;
     b.h_sizes = ctx->h_sizes;
-    auto sync = [&]() {
-        if (b.status != FL_OK) return;
-        hipError_t he = hipStreamSynchronize(ctx->stream);
-        if (he != hipSuccess) build_fail(b, FL_EHIP, "%s", hipGetErrorString(he));
-    };
     build_begin(ctx, b, space, d_fitness_raw, nb);
-    sync();
+    build_wait(ctx, b);
     build_degree(ctx, b);
-    sync();
+    build_wait(ctx, b);
     build_fill(ctx, b);
-    (void)hipStreamSynchronize(ctx->stream);
+    const hipError_t he = hipStreamSynchronize(ctx->stream);
+    if (he != hipSuccess && b.status == FL_OK) build_fail(b, FL_EHIP, "%s", hipGetErrorString(he));
     build_end(ctx, b);
     if (b.status != FL_OK) {
         build_abort(ctx, b);
@@ -1262,16 +1326,14 @@ struct Progress {
     bool stopped = false;
     double resid = 0.0;
 };
-Progress read_progress(const uint64_t *word) {
+void read_progress(const uint64_t *word, Progress &p) {
     const uint64_t w = __atomic_load_n(word, __ATOMIC_ACQUIRE);
-    Progress p;
     p.sweep = (int32_t)((w >> 32) & 0x7fffffffu);
     p.stopped = (w >> 63) & 1;
     float r;
     const uint32_t lo = (uint32_t)w;
     memcpy(&r, &lo, 4);
     p.resid = (double)r;
-    return p;
 }
 
 // The sweeps of the lagged step.  Every sweep's step reports to a pinned host
@@ -1292,7 +1354,7 @@ fl_status run_lagged(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int 
     __atomic_store_n(ctx->h_progress, uint64_t(0), __ATOMIC_RELEASE);
     a.progress = ctx->h_progress;
     int64_t launches = 0, ahead = kSweepLead;
-    Progress seen;
+    Progress seen, now;
     uint32_t idle = 0;
     for (;;) {
         const bool room = launches < std::min(limit, seen.sweep + ahead);
@@ -1309,7 +1371,7 @@ fl_status run_lagged(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int 
             if (timed_here) FL_HIP(hipEventRecord(ctx->sweep_ev[2 * pair + 1], s));
             ++launches;
         }
-        const Progress now = read_progress(ctx->h_progress);
+        read_progress(ctx->h_progress, now);
         if (now.stopped) break;
         if (now.sweep > seen.sweep) {
             // sweeps until the residual falls below the tolerance at the rate
@@ -1326,7 +1388,8 @@ fl_status run_lagged(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int 
             const hipError_t q = hipStreamQuery(s);
             if (q == hipErrorNotReady) (void)hipGetLastError();
             if (q != hipSuccess && q != hipErrorNotReady) FL_HIP(q);
-            if (q == hipSuccess && launches >= limit && !read_progress(ctx->h_progress).stopped)
+            read_progress(ctx->h_progress, now);
+            if (q == hipSuccess && launches >= limit && !now.stopped)
                 return fail(ctx, FL_EHIP, "the iteration did not stop after %lld sweeps", (long long)launches);
         } else if (!room) {
             __builtin_ia32_pause();
@@ -1376,9 +1439,10 @@ fl_status run_separate(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, in
 }
 
 // PageRank, minima and C_p of a built plan.  quiet: no timing events are
-// created or recorded and no sweep is profiled (fl_analyze_noalloc).
+// created or recorded and no sweep is profiled (one-shot analyses).  The node
+// map is copied to d_valid_raw if that is given.
 fl_status execute_impl(fl_ctx *ctx, fl_plan *p, const fl_params *prm, double *d_pagerank, int32_t *d_minima,
-                       fl_summary *out, bool exact, bool quiet = false) {
+                       fl_summary *out, bool exact, bool quiet = false, int32_t *d_valid_raw = nullptr) {
     if (!ctx) return FL_EINVAL;
     ctx->err.clear();
     if (!p || !prm || !d_pagerank || (!d_minima && p->m > 0)) return fail(ctx, FL_EINVAL, "null argument");
@@ -1386,11 +1450,7 @@ fl_status execute_impl(fl_ctx *ctx, fl_plan *p, const fl_params *prm, double *d_
     Resolved r;
     fl_status st = resolve_params(ctx, p, prm, r, exact);
     if (st != FL_OK) return st;
-    int lanes = r.lanes;
-    if (prm->row_mapping == 0) {
-        const auto hit = ctx->tuned.find(shape_key(p));
-        if (hit != ctx->tuned.end()) lanes = hit->second;
-    }
+    const int lanes = layout_of(ctx, p, prm);
     FL_HIP(hipSetDevice(ctx->device));
     hipStream_t s = ctx->stream;
     PrArgs a;
@@ -1411,7 +1471,7 @@ fl_status execute_impl(fl_ctx *ctx, fl_plan *p, const fl_params *prm, double *d_
     if (st != FL_OK) return st;
     if (timed) FL_HIP(hipEventRecord(p->ev[6], s));
     if (timed) FL_HIP(hipEventRecord(p->ev[3], s));
-    FL_HIP(fl::launch_pr_output(a, d_pagerank, p->minima, (int32_t)p->m, d_minima, s));
+    FL_HIP(fl::launch_pr_output(a, d_pagerank, p->minima, (int32_t)p->m, d_minima, d_valid_raw, s));
     const double threshold = (1.0 + r.p) * (double)p->f_opt;
     FL_HIP(fl::launch_score(d_pagerank, p->minima, (int32_t)p->m, p->fit_c, threshold, p->state, s));
     if (timed) FL_HIP(hipEventRecord(p->ev[4], s));
@@ -1552,24 +1612,49 @@ fl_status fl_plan_destroy(fl_ctx *ctx, fl_plan *p) {
     return FL_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// Build, PageRank, minima and C_p of a space whose plan nobody keeps (in place
+// in *plan, buffers from the pool or the installed arena): stages wait only
+// for the sizes that the next one needs, and the stream is idle on return.
+fl_status analyze_once(fl_ctx *ctx, const fl_space *space, const float *d_fitness_raw, fl_neighbourhood nb,
+                       const fl_params *params, double *d_pagerank, int32_t *d_minima, int32_t *d_valid_raw,
+                       fl_summary *out) {
+    fl_plan plan;
+    Build b;
+    b.h_sizes = ctx->h_sizes;
+    b.timed = false;
+    b.storage = &plan;
+    b.once = params;
+    build_begin(ctx, b, space, d_fitness_raw, nb);
+    build_wait(ctx, b);
+    build_degree(ctx, b);
+    build_wait(ctx, b);
+    build_fill(ctx, b);
+    fl_status st = b.status;
+    if (st == FL_OK) {
+        st = execute_impl(ctx, &plan, params, d_pagerank, d_minima, out, false, true, d_valid_raw);
+    } else {
+        fail(ctx, st, "%s", b.err.c_str());
+    }
+    if (st != FL_OK && st != FL_ENOCONV) (void)hipStreamSynchronize(ctx->stream);
+    build_abort(ctx, b);   // every buffer back to the pool
+    return st;
+}
+
+}  // namespace
+
+extern "C" {
+
 fl_status fl_analyze(fl_ctx *ctx, const fl_space *space, const float *d_fitness_raw, fl_neighbourhood nb,
                      const fl_params *params, double *d_pagerank, int32_t *d_minima, int32_t *d_valid_raw,
                      fl_summary *out) {
     if (!ctx) return FL_EINVAL;
-    fl_plan *p = nullptr;
-    fl_status st = fl_plan_create(ctx, space, d_fitness_raw, nb, &p, nullptr);
-    if (st != FL_OK) return st;
-    st = fl_execute(ctx, p, params, d_pagerank, d_minima, out);
-    if (st == FL_OK || st == FL_ENOCONV) {
-        const std::string msg = ctx->err;
-        const fl_status xs = fl_plan_export(ctx, p, d_valid_raw, nullptr, nullptr, nullptr);
-        if (xs != FL_OK) st = xs;
-        else ctx->err = msg;
-    }
-    const std::string msg = ctx->err;
-    fl_plan_destroy(ctx, p);
-    ctx->err = msg;
-    return st;
+    ctx->err.clear();
+    FL_HIP(hipSetDevice(ctx->device));
+    return analyze_once(ctx, space, d_fitness_raw, nb, params, d_pagerank, d_minima, d_valid_raw, out);
 }
 
 fl_status fl_analyze_noalloc(fl_ctx *ctx, const fl_space *space, const float *d_fitness_raw, fl_neighbourhood nb,
@@ -1598,36 +1683,8 @@ fl_status fl_analyze_noalloc(fl_ctx *ctx, const fl_space *space, const float *d_
     arena.base = static_cast<char *>(ctx->scratch);
     arena.cap = kNoAllocScratchBytes;
     ctx->arena = &arena;
-    fl_plan plan;   // built in place: no host allocation either
-    Build b;
-    b.h_sizes = ctx->h_sizes;
-    b.timed = false;
-    b.storage = &plan;
-    auto sync = [&]() {
-        if (b.status != FL_OK) return;
-        hipError_t he = hipStreamSynchronize(ctx->stream);
-        if (he != hipSuccess) build_fail(b, FL_EHIP, "%s", hipGetErrorString(he));
-    };
-    build_begin(ctx, b, space, d_fitness_raw, nb);
-    sync();
-    build_degree(ctx, b);
-    sync();
-    build_fill(ctx, b);
-    (void)hipStreamSynchronize(ctx->stream);
-    build_end(ctx, b);
-    fl_status st = b.status;
-    if (st == FL_OK) {
-        st = execute_impl(ctx, &plan, params, d_pagerank, d_minima, out, false, true);
-        if ((st == FL_OK || st == FL_ENOCONV) && d_valid_raw) {
-            const hipError_t he = hipMemcpyAsync(d_valid_raw, plan.valid_raw, 4 * plan.n, hipMemcpyDeviceToDevice,
-                                                 ctx->stream);
-            const hipError_t hs = hipStreamSynchronize(ctx->stream);
-            if (he != hipSuccess || hs != hipSuccess) st = fail(ctx, FL_EHIP, "node map copy failed");
-        }
-    } else {
-        (void)hipStreamSynchronize(ctx->stream);
-        fail(ctx, st, "%s", b.err.c_str());
-    }
+    // built in place: no host allocation either
+    fl_status st = analyze_once(ctx, space, d_fitness_raw, nb, params, d_pagerank, d_minima, d_valid_raw, out);
     ctx->arena = nullptr;
     if (arena.overflow)
         st = fail(ctx, FL_EINVAL,
@@ -1894,19 +1951,9 @@ fl_status fl_batch_add(fl_ctx *ctx, fl_batch *b, fl_plan *p, const fl_params *pr
     // binned sweep with the plan's bins (built here, with the class's tuned
     // mapping, if the plan is this context's and has none)
     const bool slot_ok = p->sl.words > 0 && x_bytes_of(p) > 0;
-    bool binned;
-    if (is_slot_layout(prm->row_mapping)) {
-        if (!slot_ok) return fail(ctx, FL_EINVAL, "the slot sweep cannot take a space of 2^29+ configurations");
-        binned = false;
-    } else if (is_binned_layout(prm->row_mapping)) {
-        binned = true;
-    } else {
-        // a tuned lanes-per-row CSR layout wins on a lone space by spreading
-        // it over more workgroups; in a batch the members supply that
-        // parallelism, so such members keep the slot sweep
-        const auto hit = ctx->tuned.find(shape_key(p));
-        binned = !slot_ok || (hit != ctx->tuned.end() && hit->second == FL_ROWS_BINNED);
-    }
+    if (is_slot_layout(prm->row_mapping) && !slot_ok)
+        return fail(ctx, FL_EINVAL, "the slot sweep cannot take a space of 2^29+ configurations");
+    bool binned = member_binned(ctx, p, prm);
     if (binned) {
         if (p->ctx == ctx) {
             st = ensure_binned(ctx, p, bin_map_for(ctx, shape_key(p)));
@@ -2326,6 +2373,7 @@ fl_status fl_analyze_batch(fl_ctx *ctx, int32_t n_spaces, const fl_space *spaces
         bd.timed = false;
         bd.shared_sizes = true;
         bd.defer = true;
+        bd.once = &prm[j];
         bd.h_sizes = h_sizes + j;
         bd.d_sizes = d_sizes + j;
         build_begin(ctx, bd, &spaces[j], d_fitness_raw[j], nb[j]);
@@ -2360,6 +2408,7 @@ fl_status fl_analyze_batch(fl_ctx *ctx, int32_t n_spaces, const fl_space *spaces
     if (he == hipSuccess) he = stage_sync();
     // stages 2 and 3 run the slot builds grouped by (record width, buffer form)
     int64_t group_begin[fl::kMaxWords + 1][2] = {}, group_count[fl::kMaxWords + 1][2] = {};
+    int64_t minima_begin = 0;
     auto group_tiles = [&]() -> hipError_t {
         int64_t total = 0;
         for (auto &bd : builds)
@@ -2372,12 +2421,17 @@ fl_status fl_analyze_batch(fl_ctx *ctx, int32_t n_spaces, const fl_space *spaces
                 group_begin[w][q] = nt;
                 for (int32_t j = 0; j < n_spaces; ++j) {
                     const Build &bd = builds[j];
-                    if (bd.status != FL_OK || bd.p->sl.words != w || (int)buf_of(bd.p) != q) continue;
+                    if (bd.status != FL_OK || bd.p->sl.words != w || (int)buf_of(bd.p) != q || bd.slots_only) continue;
                     for (int32_t t = 0; t < tiles_of(bd.p); ++t) ctx->h_seg_tiles[nt++] = {j, t};
                     hid[n_ids++] = j;
                 }
                 group_count[w][q] = nt - group_begin[w][q];
             }
+        // (stage 3) the spaces that get their minima alone
+        minima_begin = nt;
+        for (int32_t j = 0; j < n_spaces; ++j)
+            if (builds[j].status == FL_OK && builds[j].slots_only)
+                for (int32_t t = 0; t < tiles_of(builds[j].p); ++t) ctx->h_seg_tiles[nt++] = {j, t};
         return hipSuccess;
     };
     // stage 2: degree count (allocations in build_degree; generic spaces launch there)
@@ -2415,7 +2469,7 @@ fl_status fl_analyze_batch(fl_ctx *ctx, int32_t n_spaces, const fl_space *spaces
     if (he == hipSuccess) he = stage_sync();
     // stage 3: CSR fill (col_idx allocated in build_fill; generic spaces launch there)
     if (he == hipSuccess) {
-        for (auto &bd : builds) build_fill(ctx, bd);
+        for (auto &bd : builds) build_fill(ctx, bd, false);
         he = group_tiles();
     }
     for (int32_t j = 0; j < n_spaces && he == hipSuccess; ++j) {
@@ -2434,6 +2488,7 @@ fl_status fl_analyze_batch(fl_ctx *ctx, int32_t n_spaces, const fl_space *spaces
             if (group_count[w][q] > 0)
                 he = fl::launch_seg_fill(d_segs, d_tiles + group_begin[w][q], (int32_t)group_count[w][q], w,
                                          q != 0, s);
+    if (he == hipSuccess) he = fl::launch_seg_minima(d_segs, d_tiles + minima_begin, (int32_t)(nt - minima_begin), s);
     const hipError_t hf = hipStreamSynchronize(s);
     if (he == hipSuccess) he = hf;
     for (auto &bd : builds) {

@@ -87,7 +87,23 @@ struct BuildSizes {
     int32_t n_minima;
     int64_t n_edges;
     int32_t n_plateau;   // minima with a neighbour of equal fitness
-    int32_t pad;
+    uint32_t stamp;      // host copy: the stage's stamp, stored after everything else
+};
+
+// Where a build stage reports its sizes besides device memory: a pinned copy
+// (or null) and the stamp the host waits for there.
+struct HostSizes {
+    BuildSizes *sizes;
+    uint32_t stamp;
+};
+
+// In-edge lists per wave of 64 consecutive nodes: wave w's quad u of lane l is
+// quad[(w * stride + u) * 64 + l], four byte offsets into x; quads[w] of them
+// are used, a positive multiple of kListQuads.
+struct WaveLists {
+    uint4 *quad;
+    int32_t *quads;
+    int32_t stride;
 };
 
 // One space of a segmented build: every space of a batch runs each build
@@ -112,6 +128,7 @@ struct SegBuild {
     int32_t *tile_m, *tile_moff;
     // CSR fill (after the degree pass: E)
     int32_t *row_ptr, *col_idx, *minima;
+    WaveLists lists;
     int32_t c_tiles, n_tiles, n, n_edges, k_pad, fit_bytes, remap_bytes, pad;
 };
 struct SegTile {
@@ -152,15 +169,6 @@ enum SweepKind : int32_t {
     kSweepSlots = 1,  // pull over the records' in-edge slot bits, x indexed by raw index
     kSweepBinned = 2, // pull over the CSR with rows binned by in-degree, each bin its own lanes per row
     kSweepLists = 3   // pull over the waves' in-edge lists, x indexed by node id (n + 1 entries, the last 0)
-};
-
-// In-edge lists per wave of 64 consecutive nodes: wave w's quad u of lane l is
-// quad[(w * stride + u) * 64 + l], four byte offsets into x; quads[w] of them
-// are used, a positive multiple of kListQuads.
-struct WaveLists {
-    uint4 *quad;
-    int32_t *quads;
-    int32_t stride;
 };
 
 // Rows binned by in-degree: bucket 0 holds in-degree 0, bucket b >= 1 the
@@ -286,7 +294,7 @@ struct TileRef {
 // tile_min and tile_bad hold ceil(n_raw / kSingleTile) entries.
 hipError_t launch_compact_single(const float *fit, int32_t n_raw, int32_t *tile_cnt, float *tile_min,
                                  int32_t *tile_bad, int32_t *remap, int32_t *valid_raw, float *fit_c,
-                                 BuildSizes *sizes, hipStream_t stream);
+                                 BuildSizes *sizes, const HostSizes &host, hipStream_t stream);
 // Segmented build stages (see SegBuild): `tiles` lists (space, tile) pairs,
 // `ids` the spaces of the one-workgroup-per-space scans.
 hipError_t launch_seg_compact(const SegBuild *segs, const SegTile *tiles, int32_t n_tiles, const int32_t *ids,
@@ -300,12 +308,18 @@ hipError_t launch_degree(const SpaceDesc &sp, const SlotTable &sl, int adjacent,
                          const int32_t *valid_raw, int32_t n, int32_t *in_deg, int32_t *out_deg,
                          uint64_t *rec, uint64_t *presence, int32_t *off_table, int32_t k_pad,
                          int64_t *tile_e, int32_t *tile_m, int64_t *tile_eoff, int32_t *tile_moff,
-                         BuildSizes *sizes, hipStream_t stream);
+                         BuildSizes *sizes, const HostSizes &host, hipStream_t stream);
 hipError_t launch_fill(const SpaceDesc &sp, const SlotTable &sl, int adjacent, const float *fit,
                        const int32_t *valid_raw, const int32_t *remap, const uint64_t *rec,
                        const uint64_t *presence, int32_t n, int32_t n_edges, const int32_t *in_deg,
                        const int32_t *out_deg, const int64_t *tile_eoff, const int32_t *tile_moff,
-                       int32_t *row_ptr, int32_t *col_idx, int32_t *minima, hipStream_t stream);
+                       int32_t *row_ptr, int32_t *col_idx, int32_t *minima, const WaveLists *lists,
+                       hipStream_t stream);
+// What a slot space's fill leaves when its CSR is not wanted: with `lists` the
+// lists instead of the CSR, with launch_fill_minima the minima alone.
+hipError_t launch_fill_minima(const int32_t *out_deg, int32_t n, const int32_t *tile_moff, int32_t *minima,
+                              hipStream_t stream);
+hipError_t launch_seg_minima(const SegBuild *segs, const SegTile *tiles, int32_t n_tiles, hipStream_t stream);
 hipError_t launch_pr_init(const PrArgs &a, int grid, hipStream_t stream);
 hipError_t launch_pr_iter(const PrArgs &a, const SpaceDesc &sp, const SlotTable &sl, int lanes,
                           int grid, hipStream_t stream);
@@ -318,7 +332,7 @@ hipError_t pr_iter_blocks_per_cu(const PrArgs &a, const SpaceDesc &sp, const Slo
 hipError_t launch_make_lists(const int32_t *row_ptr, const int32_t *col_idx, int32_t n, const WaveLists &wl,
                              hipStream_t stream);
 hipError_t launch_pr_output(const PrArgs &a, double *pagerank, const int32_t *minima, int32_t m, int32_t *out_minima,
-                            hipStream_t stream);
+                            int32_t *out_valid, hipStream_t stream);
 // Binning of the rows by in-degree class: class_of[b] is the class of bucket
 // b.  Count per (class, node tile) into cnt (kBuckets x n_tiles, class-major),
 // scan it into off and totals (kBuckets entries), write bin_rows.
