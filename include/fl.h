@@ -312,10 +312,10 @@ fl_status fl_analyze_noalloc(fl_ctx *ctx, const fl_space *space, const float *d_
 /* ---- Batches: many spaces in one segmented PageRank (continuous batching) ----
  *
  * A batch runs the power iteration of many plans together: every sweep is one
- * segmented launch over the tiles of all running members (one launch per
- * node-record width of the slot-sweep members, one for the binned members),
- * followed by one launch that finishes the step of every member.  Each member keeps its own damping, tolerance, iteration count and
- * stop flag, and its results equal those of fl_execute with the slot sweep
+ * segmented launch over the tiles of all running members (one for the
+ * slot-sweep members, one for the binned members), followed by one launch
+ * that finishes the step of every member.  Each member keeps its own damping,
+ * tolerance, iteration count and stop flag, and its results equal those of fl_execute with the slot sweep
  * (row_mapping FL_ROWS_SLOTS, flags FL_STEP_SEPARATE) bit for bit, whatever
  * else runs in the batch.  A batch ignores FL_STEP_SEPARATE in the
  * parameters: its members always take a step kernel per sweep.
@@ -362,7 +362,7 @@ fl_status fl_batch_add(fl_ctx *ctx, fl_batch *batch, fl_plan *plan, const fl_par
  * members that converge or reach max_iter finish: their ranks,
  * minima and C_p (Sec. VII-B, eq. 3) are written.  *n_running receives the
  * number of members not yet finished.  The sweep loop of a step (per sweep:
- * one launch per node-record width, then the step launch) is captured once
+ * one launch per kind of sweep, then the step launch) is captured once
  * per launch shape (the number of sweeps and grid sizes rounded to powers of
  * two) in a HIP graph and replayed by later steps of that shape; the batch
  * keeps the graphs of its 256 most recently used shapes and drops them all
@@ -388,7 +388,7 @@ fl_status fl_batch_set_graphs(fl_ctx *ctx, fl_batch *batch, int32_t enable);
 
 /* Members of at most max_tiles tiles of 256 nodes (default 16, i.e. up to
  * 4096 nodes; 0 = none; at most 64) iterate inside one workgroup each: one
- * launch per record width and step runs up to 4 x `sweeps` of their sweeps
+ * launch per step runs up to 4 x `sweeps` of their sweeps
  * and steps back to back (until they stop), on a second stream of the
  * batch, while the other members' sweep loop runs on the context's stream.
  * Their results equal the plain slot sweep's bit for bit as well.  Takes

@@ -148,6 +148,7 @@ struct fl_ctx {
     DevicePool pool;
     std::map<uint64_t, int> tuned;  // shape class -> sweep layout chosen by fl_tune
     std::map<uint64_t, uint64_t> tuned_map;  // shape class -> in-degree bucket mapping chosen by fl_tune
+    char *h_page = nullptr;         // one pinned page that holds the pinned words below
     int32_t *h_bins = nullptr;      // pinned: bucket classes out, class sizes back
     int32_t profile_every = 0;      // bracket every n-th sweep kernel with events (fl_profile), 0 = off
     std::vector<hipEvent_t> sweep_ev;  // 2 per launch of the longest chunk so far
@@ -1037,8 +1038,9 @@ struct fl_batch {
     // members) in the sweep list, [kRunCount] running members, [kInitCount]
     // joining ones
     static constexpr int kRunCount = 2 * fl::kMaxWords + 2, kInitCount = kRunCount + 1, kCounts = 16;
+    static constexpr int kKinds = 2;   // sweep launches: binned members, slot members of every width
     int32_t *d_counts = nullptr, *h_counts = nullptr;
-    int sweep_per_cu[fl::kMaxWords + 1] = {};
+    int sweep_per_cu[kKinds] = {};
     int64_t sweeps = 0;
     double sweep_ms = 0.0;
     hipEvent_t ev[2] = {};
@@ -1054,13 +1056,13 @@ struct fl_batch {
     hipEvent_t fork = nullptr, join = nullptr;
     struct Shape {
         int32_t sweeps = 0, finish_grid = 0;
-        int32_t grid[fl::kMaxWords + 1] = {};
+        int32_t grid[kKinds] = {};
         const void *members = nullptr, *tiles = nullptr, *ids = nullptr;
         bool operator==(const Shape &o) const {
             if (sweeps != o.sweeps || finish_grid != o.finish_grid || members != o.members || tiles != o.tiles ||
                 ids != o.ids)
                 return false;
-            for (int w = 0; w <= fl::kMaxWords; ++w)
+            for (int w = 0; w < kKinds; ++w)
                 if (grid[w] != o.grid[w]) return false;
             return true;
         }
@@ -1230,19 +1232,19 @@ fl_status fl_create(fl_ctx **out, int device, void *hip_stream) {
     ctx->stream = static_cast<hipStream_t>(hip_stream);
     if (hipSetDevice(device) != hipSuccess ||
         hipDeviceGetAttribute(&ctx->num_cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
-        hipHostMalloc((void **)&ctx->h_sizes, sizeof(BuildSizes), hipHostMallocCoherent) != hipSuccess ||
-        hipHostMalloc((void **)&ctx->h_state, sizeof(PrState), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&ctx->h_progress, 64, hipHostMallocCoherent) != hipSuccess ||
-        hipHostMalloc((void **)&ctx->h_bins, sizeof(int32_t) * 64, hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void **)&ctx->h_page, 4096, hipHostMallocCoherent) != hipSuccess ||
         scratch_address(device, &ctx->scratch) != hipSuccess) {
         (void)hipGetLastError();
-        if (ctx->h_sizes) (void)hipHostFree(ctx->h_sizes);
-        if (ctx->h_state) (void)hipHostFree(ctx->h_state);
-        if (ctx->h_progress) (void)hipHostFree(ctx->h_progress);
-        if (ctx->h_bins) (void)hipHostFree(ctx->h_bins);
+        if (ctx->h_page) (void)hipHostFree(ctx->h_page);
         delete ctx;
         return FL_EHIP;
     }
+    static_assert(sizeof(PrState) <= 1024 && sizeof(BuildSizes) <= 256, "the page's parts");
+    memset(ctx->h_page, 0, 4096);
+    ctx->h_progress = reinterpret_cast<uint64_t *>(ctx->h_page);
+    ctx->h_sizes = reinterpret_cast<BuildSizes *>(ctx->h_page + 256);
+    ctx->h_bins = reinterpret_cast<int32_t *>(ctx->h_page + 512);
+    ctx->h_state = reinterpret_cast<PrState *>(ctx->h_page + 1024);
     *out = ctx;
     return FL_OK;
 }
@@ -1258,10 +1260,7 @@ fl_status fl_destroy(fl_ctx *ctx) {
     (void)hipHostFree(ctx->h_seg_sizes);
     ctx->pool.release_all();
     for (hipEvent_t e : ctx->sweep_ev) (void)hipEventDestroy(e);
-    (void)hipHostFree(ctx->h_sizes);
-    (void)hipHostFree(ctx->h_state);
-    (void)hipHostFree(ctx->h_progress);
-    (void)hipHostFree(ctx->h_bins);
+    (void)hipHostFree(ctx->h_page);
     delete ctx;
     return FL_OK;
 }
@@ -1863,9 +1862,9 @@ fl_status fl_batch_create(fl_ctx *ctx, fl_batch **out) {
     fl_batch *b = new (std::nothrow) fl_batch;
     if (!b) return fail(ctx, FL_ENOMEM, "out of host memory");
     b->ctx = ctx;
-    for (int w = 0; w <= fl::kMaxWords; ++w) {
+    for (int w = 0; w < fl_batch::kKinds; ++w) {
         hipError_t he = w == 0 ? fl::batch_sweep_binned_blocks_per_cu(&b->sweep_per_cu[0])
-                               : fl::batch_sweep_blocks_per_cu(w, &b->sweep_per_cu[w]);
+                               : fl::batch_sweep_blocks_per_cu(&b->sweep_per_cu[1]);
         if (he != hipSuccess) {
             delete b;
             return fail(ctx, FL_EHIP, "occupancy query: %s", hipGetErrorString(he));
@@ -2059,12 +2058,12 @@ fl_status fl_batch_step(fl_ctx *ctx, fl_batch *b, int32_t sweeps, int32_t *n_run
         m.phase = 1;
     }
     // running members: those the segmented launches sweep first (their ids
-    // are the step kernel's list), then the small ones grouped by width
+    // are the step kernel's list), then the small ones
     auto small = [&](const fl_batch::Member &m) {
         return !m.binned && b->small_tiles > 0 && tiles_of(m.plan) <= b->small_tiles;
     };
-    auto width = [](const fl_batch::Member &m) { return m.binned ? 0 : m.plan->sl.words; };
     int32_t n_run = 0;
+    auto width = [](const fl_batch::Member &m) { return m.binned ? 0 : m.plan->sl.words; };
     int64_t group_begin[fl::kMaxWords + 2] = {};
     int64_t nt = 0;
     for (int w = 0; w <= fl::kMaxWords; ++w) {
@@ -2077,14 +2076,9 @@ fl_status fl_batch_step(fl_ctx *ctx, fl_batch *b, int32_t sweeps, int32_t *n_run
         }
     }
     group_begin[fl::kMaxWords + 1] = nt;
-    int32_t small_begin[fl::kMaxWords + 2] = {};
     int32_t n_all = n_run;
-    for (int w = 1; w <= fl::kMaxWords; ++w) {
-        small_begin[w] = n_all;
-        for (auto &m : b->members)
-            if (m.phase == 1 && width(m) == w && small(m)) i_run[n_all++] = m.slot;
-    }
-    small_begin[fl::kMaxWords + 1] = n_all;
+    for (auto &m : b->members)
+        if (m.phase == 1 && small(m)) i_run[n_all++] = m.slot;
     int32_t *hc = b->h_counts;
     memset(hc, 0, sizeof(int32_t) * fl_batch::kCounts);
     for (int w = 0; w <= fl::kMaxWords; ++w) {
@@ -2115,12 +2109,8 @@ fl_status fl_batch_step(fl_ctx *ctx, fl_batch *b, int32_t sweeps, int32_t *n_run
     if (side) {
         FL_HIP(hipEventRecord(b->fork, s));
         FL_HIP(hipStreamWaitEvent(b->side_stream, b->fork, 0));
-        for (int w = 1; w <= fl::kMaxWords; ++w) {
-            const int32_t cnt = small_begin[w + 1] - small_begin[w];
-            if (cnt == 0) continue;
-            FL_HIP(fl::launch_batch_small(b->d_members, d_run + small_begin[w], cnt, w, 4 * sweeps,
-                                          std::min(cnt, 1024), b->side_stream));
-        }
+        FL_HIP(fl::launch_batch_small(b->d_members, d_run + n_run, n_all - n_run, 4 * sweeps,
+                                      std::min(n_all - n_run, 1024), b->side_stream));
         FL_HIP(hipEventRecord(b->join, b->side_stream));
     }
     if (n_run > 0 && sweeps > 0) {
@@ -2132,8 +2122,8 @@ fl_status fl_batch_step(fl_ctx *ctx, fl_batch *b, int32_t sweeps, int32_t *n_run
         shape.members = b->d_members;
         shape.tiles = b->d_tiles;
         shape.ids = b->d_ids;
-        for (int w = 0; w <= fl::kMaxWords; ++w) {
-            const int32_t cnt = hc[2 * w + 1];
+        for (int w = 0; w < fl_batch::kKinds; ++w) {
+            const int32_t cnt = w == 0 ? hc[1] : (int32_t)(nt - group_begin[1]);
             if (cnt == 0) continue;
             const int64_t resident =
                 (int64_t)std::max(b->sweep_per_cu[w], 1) * ctx->num_cus / fl::kXcds * fl::kXcds;
@@ -2146,12 +2136,11 @@ fl_status fl_batch_step(fl_ctx *ctx, fl_batch *b, int32_t sweeps, int32_t *n_run
         shape.finish_grid = fg;
         auto enqueue = [&](hipStream_t q) -> hipError_t {
             for (int32_t j = 0; j < sweeps; ++j) {
-                for (int w = 0; w <= fl::kMaxWords; ++w) {
+                for (int w = 0; w < fl_batch::kKinds; ++w) {
                     if (shape.grid[w] == 0) continue;
                     hipError_t e = w == 0 ? fl::launch_batch_sweep_binned(b->d_members, d_sweep, b->d_counts,
                                                                           shape.grid[0], q)
-                                          : fl::launch_batch_sweep(b->d_members, d_sweep, b->d_counts + 2 * w, w,
-                                                                   shape.grid[w], q);
+                                          : fl::launch_batch_sweep(b->d_members, d_sweep, b->d_counts, shape.grid[w], q);
                     if (e != hipSuccess) return e;
                 }
                 hipError_t e = fl::launch_batch_finish(b->d_members, d_run, b->d_counts + fl_batch::kRunCount,

@@ -366,15 +366,15 @@ hipError_t launch_naive(const int32_t *minima, int32_t m, const float *fit_c, fl
 hipError_t launch_batch_init(const BatchMember *members, const TileRef *tiles, int32_t n_tiles,
                              const int32_t *member_ids, int32_t n_members, const int32_t *n_members_dev,
                              hipStream_t stream);
-hipError_t launch_batch_sweep(const BatchMember *members, const TileRef *tiles, const int32_t *range_dev,
-                              int words, int grid, hipStream_t stream);
-hipError_t batch_sweep_blocks_per_cu(int words, int *blocks);
+hipError_t launch_batch_sweep(const BatchMember *members, const TileRef *tiles, const int32_t *ranges_dev, int grid,
+                              hipStream_t stream);
+hipError_t batch_sweep_blocks_per_cu(int *blocks);
 hipError_t launch_batch_finish(const BatchMember *members, const int32_t *member_ids, const int32_t *n_members_dev,
                                int grid, hipStream_t stream);
-// Small members of record width `words`, one workgroup each (grid-stride):
+// Small members, one workgroup each (grid-stride):
 // up to max_sweeps sweeps and steps per member, back to back in the
 // workgroup, until it stops.
-hipError_t launch_batch_small(const BatchMember *members, const int32_t *member_ids, int32_t n_members, int words,
+hipError_t launch_batch_small(const BatchMember *members, const int32_t *member_ids, int32_t n_members,
                               int32_t max_sweeps, int grid, hipStream_t stream);
 hipError_t launch_batch_output(const BatchMember *members, const TileRef *tiles, int32_t n_tiles,
                                const int32_t *member_ids, int32_t n_members, PrState *states_out,
