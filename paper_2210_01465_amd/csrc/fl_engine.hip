@@ -352,31 +352,30 @@ fl::SlotTable make_slots(const SpaceDesc &sp, bool adjacent) {
     std::sort(slots, slots + n_slots, [](const Slot &x, const Slot &y) { return x.off < y.off; });
     for (int s = 0; s < n_slots; ++s) {
         t.off[s] = (int32_t)slots[s].off;
-        t.delta[s] = (int16_t)slots[s].delta;
-        t.dim[s] = (uint8_t)slots[s].dim;
     }
     // runs of each parameter's slots (checked: a space where they were not
     // contiguous would take the generic kernels)
-    for (int k = 0; k < sp.n; ++k) {
+    for (int k = sp.n - 1; k >= 0; --k) {
         const int reach = adjacent ? std::min(1, sp.radix[k] - 1) : sp.radix[k] - 1;
-        t.blk_len[k] = (int16_t)reach;
-        t.blk_neg[k] = t.blk_pos[k] = 0;
         if (reach <= 0) continue;
         int neg = -1, pos = -1;
         for (int s = 0; s < t.k; ++s) {
-            if (t.dim[s] != k) continue;
-            if (t.delta[s] == -reach) neg = s;
-            if (t.delta[s] == 1) pos = s;
+            if (slots[s].dim != k) continue;
+            if (slots[s].delta == -reach) neg = s;
+            if (slots[s].delta == 1) pos = s;
         }
         bool ok = neg >= 0 && pos >= 0;
         for (int d = 0; ok && d < reach; ++d)
-            ok = t.dim[neg + d] == k && t.delta[neg + d] == d - reach && t.dim[pos + d] == k && t.delta[pos + d] == d + 1;
+            ok = slots[neg + d].dim == k && slots[neg + d].delta == d - reach && slots[pos + d].dim == k &&
+                 slots[pos + d].delta == d + 1;
         if (!ok) {
             t.words = 0;
             return t;
         }
-        t.blk_neg[k] = (int16_t)neg;
-        t.blk_pos[k] = (int16_t)pos;
+        int l = 1;
+        while ((1ll << l) < sp.radix[k]) ++l;
+        const uint64_t num = 1ull << (31 + l), d = (uint64_t)sp.radix[k];
+        t.par[t.n_par++] = {(uint32_t)((num + d - 1) / d), (uint32_t)(l - 1), sp.radix[k], neg, pos, reach};
     }
     return t;
 }

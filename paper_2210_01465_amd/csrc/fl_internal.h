@@ -56,8 +56,8 @@ struct SpaceDesc {
 };
 
 // Candidate neighbour slots, numbered independently of the node: slot s moves
-// parameter dim[s] by delta[s] list positions, i.e. to raw index i + off[s]
-// with off[s] = delta[s] * stride[dim[s]].  Hamming (eq. 2) gives parameter k
+// one parameter by delta list positions, i.e. to raw index i + off[s] with
+// off[s] = delta * stride of the parameter.  Hamming (eq. 2) gives parameter k
 // the 2(radix_k - 1) deltas +-1 .. +-(radix_k - 1); adjacent gives +-1.  A
 // slot exists for a node iff 0 <= x_k + delta < radix_k.  Slots are sorted by
 // off, so ascending slot order is ascending neighbour raw index (= node id).
@@ -66,17 +66,26 @@ struct SpaceDesc {
 // of the node; in the last word, bits 24..31 hold out_deg and bits 32..63 the
 // raw index.  words = 0 when k + 40 > 64 * kMaxWords (then only the generic
 // kernels and the CSR sweep are used).
+//
+// A parameter's slots form two contiguous runs in slot order (every offset of
+// a less significant parameter is below the stride of a more significant
+// one): deltas -len..-1 at [neg, neg + len) and +1..+len at [pos, pos + len).
+// par holds them with the parameter's divisor, in whole words of one scalar
+// load, for the parameters of more than one value, least significant first:
+// q / radix = mulhi(q, magic) >> shift for every q < 2^31 (magic =
+// ceil(2^(31 + l) / radix) with 2^(l - 1) < radix <= 2^l, so magic < 2^32 and
+// magic * radix - 2^(31 + l) < radix <= 2^l; Granlund and Montgomery 1994).
+struct SlotParam {
+    uint32_t magic, shift;
+    int32_t radix;
+    int32_t neg, pos, len;
+};
 struct SlotTable {
     int32_t k;
     int32_t words;
+    int32_t n_par;
     int32_t off[kMaxSlots];
-    int16_t delta[kMaxSlots];
-    uint8_t dim[kMaxSlots];
-    // Parameter k's slots form two contiguous runs in slot order (every
-    // offset of a less significant parameter is below the stride of a more
-    // significant one): deltas -len..-1 at [neg[k], neg[k] + len[k]) and
-    // +1..+len at [pos[k], pos[k] + len[k]).
-    int16_t blk_neg[kMaxParams], blk_pos[kMaxParams], blk_len[kMaxParams];
+    SlotParam par[kMaxParams];
 };
 
 // Sizes produced on the device by the build scans, copied to the host once.

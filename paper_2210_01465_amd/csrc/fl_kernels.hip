@@ -74,74 +74,78 @@ template <int CTRL>
 __device__ __forceinline__ int32_t dpp_move(int32_t x) {
     return (int32_t)dpp_move<CTRL>((uint32_t)x);
 }
+template <int CTRL, class T>
+__device__ __forceinline__ T dpp_move64(T x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    return __builtin_bit_cast(T, ((uint64_t)dpp_move<CTRL>((uint32_t)(u >> 32)) << 32) | dpp_move<CTRL>((uint32_t)u));
+}
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double x) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, x);
-    return __builtin_bit_cast(double, ((uint64_t)dpp_move<CTRL>((uint32_t)(u >> 32)) << 32) | dpp_move<CTRL>((uint32_t)u));
+    return dpp_move64<CTRL>(x);
+}
+template <int CTRL>
+__device__ __forceinline__ int64_t dpp_move(int64_t x) {
+    return dpp_move64<CTRL>(x);
 }
 
-__device__ __forceinline__ void exchange(float x, int o, float &a, float &b) {
-    uint32_t p, q;
-    if (o == 32) exchange32(__float_as_uint(x), p, q);
-    else exchange16(__float_as_uint(x), p, q);
-    a = __uint_as_float(p);
-    b = __uint_as_float(q);
-}
-__device__ __forceinline__ void exchange(double x, int o, double &a, double &b) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, x);
-    uint32_t pl, ql, ph, qh;
-    if (o == 32) {
-        exchange32((uint32_t)u, pl, ql);
-        exchange32((uint32_t)(u >> 32), ph, qh);
+template <class T>
+__device__ __forceinline__ void exchange(T x, int o, T &a, T &b) {
+    if constexpr (sizeof(T) == 4) {
+        uint32_t p, q;
+        if (o == 32) exchange32(__builtin_bit_cast(uint32_t, x), p, q);
+        else exchange16(__builtin_bit_cast(uint32_t, x), p, q);
+        a = __builtin_bit_cast(T, p);
+        b = __builtin_bit_cast(T, q);
     } else {
-        exchange16((uint32_t)u, pl, ql);
-        exchange16((uint32_t)(u >> 32), ph, qh);
+        const uint64_t u = __builtin_bit_cast(uint64_t, x);
+        uint32_t pl, ql, ph, qh;
+        if (o == 32) {
+            exchange32((uint32_t)u, pl, ql);
+            exchange32((uint32_t)(u >> 32), ph, qh);
+        } else {
+            exchange16((uint32_t)u, pl, ql);
+            exchange16((uint32_t)(u >> 32), ph, qh);
+        }
+        a = __builtin_bit_cast(T, ((uint64_t)ph << 32) | pl);
+        b = __builtin_bit_cast(T, ((uint64_t)qh << 32) | ql);
     }
-    a = __builtin_bit_cast(double, ((uint64_t)ph << 32) | pl);
-    b = __builtin_bit_cast(double, ((uint64_t)qh << 32) | ql);
 }
 
-// Sum over the 64 lanes, valid in each: the tree of __shfl_xor from 32 down
-// to 1 (same pairs, so the same bits), as vector instructions.  Below 16
-// lanes the other lane's value is a DPP operand: after a step the lanes o
-// apart hold equal values, so a rotation by o / 2 within the row of 16 pairs
-// the same values as the exchange.
-template <typename T>
-__device__ __forceinline__ T wave_sum(T x) {
+// Reduction over the 64 lanes, valid in each: the tree of __shfl_xor from 32
+// down to 1 (same pairs, so the same bits of a sum), as vector instructions
+// instead of six dependent trips through LDS.  Below 16 lanes the other
+// lane's value is a DPP operand: after a step the lanes o apart hold equal
+// values, so a rotation by o / 2 within the row of 16 pairs the same values
+// as the exchange.
+template <class T, class F>
+__device__ __forceinline__ T wave_reduce(T x, F f) {
     T a, b;
     exchange(x, 32, a, b);
-    x = a + b;
+    x = f(a, b);
     exchange(x, 16, a, b);
-    x = a + b;
-    x += dpp_move<0x128>(x);   // row_ror:8
-    x += dpp_move<0x124>(x);   // row_ror:4
-    x += dpp_move<0x4e>(x);    // quad_perm [2,3,0,1]
-    x += dpp_move<0xb1>(x);    // quad_perm [1,0,3,2]
+    x = f(a, b);
+    x = f(x, dpp_move<0x128>(x));   // row_ror:8
+    x = f(x, dpp_move<0x124>(x));   // row_ror:4
+    x = f(x, dpp_move<0x4e>(x));    // quad_perm [2,3,0,1]
+    x = f(x, dpp_move<0xb1>(x));    // quad_perm [1,0,3,2]
     return x;
 }
-template <>
-__device__ __forceinline__ int32_t wave_sum(int32_t x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
-}
-template <>
-__device__ __forceinline__ int64_t wave_sum(int64_t x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
+
+template <typename T>
+__device__ __forceinline__ T wave_sum(T x) {
+    return wave_reduce(x, [](T a, T b) { return a + b; });
 }
 
 __device__ __forceinline__ int32_t wave_max(int32_t x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = max(x, __shfl_xor(x, o, 64));
-    return x;
+    return wave_reduce(x, [](int32_t a, int32_t b) { return max(a, b); });
 }
 
 __device__ __forceinline__ float wave_min(float x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = fminf(x, __shfl_xor(x, o, 64));
-    return x;
+    return wave_reduce(x, [](float a, float b) { return fminf(a, b); });
+}
+
+__device__ __forceinline__ uint32_t wave_or(uint32_t x) {
+    return wave_reduce(x, [](uint32_t a, uint32_t b) { return a | b; });
 }
 
 // Sum over the workgroup; the result is valid in every thread.  The fixed
@@ -270,12 +274,6 @@ __device__ __forceinline__ Record<W> load_record(const uint64_t *__restrict__ re
         for (int q = 0; q < W; ++q) r.w[q] = p[q];
     }
     return r;
-}
-
-__device__ __forceinline__ uint32_t wave_or(uint32_t x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x |= (uint32_t)__shfl_xor((int)x, o, 64);
-    return x;
 }
 
 // Number of set bits of the record's in-edge mask below slot s (compile-time
@@ -561,10 +559,20 @@ __device__ __forceinline__ void set_bits(uint64_t (&m)[W], int32_t lo, int32_t h
 // a slot no lane of the wave has is skipped with a scalar branch, and lanes
 // without it get the out-of-range buffer offset (the load returns 0, which
 // no comparison below counts).
-// SP and SL are SpaceDesc and SlotTable, either kernel arguments or entries
-// of a segment table in the constant address space (scalar loads either way).
-template <int W, bool BUF, class SP, class SL>
-__device__ __forceinline__ void degree_slots(const SP &sp, const SL &sl, int32_t tile,
+// SL is a SlotTable, either a kernel argument or an entry of a segment table
+// in the constant address space (scalar loads either way).
+// What bounds it is a wave's serial chain, at eight waves per SIMD, with the
+// texture unit's gathers (116 k of 160 k cycles at the large workload) next.
+// Half of the chain was not the gathers: the digits read each parameter's
+// runs as 16-bit members, which no scalar load takes, so three vector loads
+// waited for one after the other per parameter (now one scalar load of a
+// SlotParam, 82 -> 72 us at 1.5 M nodes and 86 slots, 62 -> 50 at 20 slots),
+// and eleven reductions went through LDS lane exchanges (wave_reduce and one
+// barrier, 72 -> 68 and 50 -> 46).  No gain: the offsets in wide scalar loads
+// ahead of the gathers, and the existence masks from a table in LDS or from
+// shifts of the uniform runs (fewer instructions, same time).
+template <int W, bool BUF, class SL>
+__device__ __forceinline__ void degree_slots(const SL &sl, int32_t tile,
                                              const float *__restrict__ fit, int32_t fit_bytes,
                                              const int32_t *__restrict__ valid_raw, int32_t n,
                                              int32_t *__restrict__ in_deg, int32_t *__restrict__ out_deg,
@@ -590,14 +598,12 @@ __device__ __forceinline__ void degree_slots(const SP &sp, const SL &sl, int32_t
     for (int q = 0; q < W; ++q) ex[q] = m[q] = 0ull;
     if (active) {
         uint32_t qv = i;
-        for (int k = sp.n - 1; k >= 0; --k) {   // digits, least significant first
-            const uint32_t qn = (uint32_t)(((uint64_t)qv * sp.magic[k]) >> sp.shift[k]);
-            const int32_t x = (int32_t)(qv - qn * (uint32_t)sp.radix[k]);
+        for (int k = 0; k < sl.n_par; ++k) {   // digits, least significant first
+            const uint32_t qn = __umulhi(qv, sl.par[k].magic) >> sl.par[k].shift;
+            const int32_t x = (int32_t)(qv - qn * (uint32_t)sl.par[k].radix);
             qv = qn;
-            const int32_t len = sl.blk_len[k];
-            if (len <= 0) continue;
-            const int32_t nb = sl.blk_neg[k], pb = sl.blk_pos[k];
-            const int32_t a = min(x, len), bcnt = min(sp.radix[k] - 1 - x, len);
+            const int32_t len = sl.par[k].len, nb = sl.par[k].neg, pb = sl.par[k].pos;
+            const int32_t a = min(x, len), bcnt = min(sl.par[k].radix - 1 - x, len);
             set_bits<W>(ex, nb + len - a, nb + len, nb, nb + len);
             set_bits<W>(ex, pb, pb + bcnt, pb, pb + len);
         }
@@ -674,10 +680,25 @@ __device__ __forceinline__ void degree_slots(const SP &sp, const SL &sl, int32_t
         hi = wave_or(hi);
         if ((threadIdx.x & 63) == 0 && v < n) presence[(int64_t)(v >> 6) * W + q] = ((uint64_t)hi << 32) | lo;
     }
-    const int64_t te = block_sum((int64_t)din);
-    const int32_t tm = block_sum((int32_t)(v < n && dout == 0));
-    const int32_t tp = block_sum((int32_t)(v < n && dout == 0 && tie));
+    // the workgroup's edges, sinks and sinks with a tie, in one exchange
+    __shared__ int32_t part[kBlock / 64][3];
+    const int32_t we = wave_sum(din);
+    const int32_t wm = __popcll(__ballot(v < n && dout == 0)), wp = __popcll(__ballot(v < n && dout == 0 && tie));
+    if ((threadIdx.x & 63) == 0) {
+        int32_t *p = part[threadIdx.x >> 6];
+        p[0] = we;
+        p[1] = wm;
+        p[2] = wp;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
+        int32_t te = 0, tm = 0, tp = 0;
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) {
+            te += part[w][0];
+            tm += part[w][1];
+            tp += part[w][2];
+        }
         tile_e[tile] = te;
         tile_m[tile] = tm;
         if (tp > 0) atomicAdd(&sizes->n_plateau, tp);
@@ -690,7 +711,7 @@ __device__ __forceinline__ void degree_slots(const SP &sp, const SL &sl, int32_t
 template <int W, bool BUF>
 __global__ __launch_bounds__(kBlock) void k_degree_slots([[maybe_unused]] SegBuild arg) {
     const_ptr<SegBuild> g = kernel_arg<SegBuild>();
-    degree_slots<W, BUF>(g->sp, g->sl, blockIdx.x, g->fit, g->fit_bytes, g->valid_raw, g->n, g->in_deg,
+    degree_slots<W, BUF>(g->sl, blockIdx.x, g->fit, g->fit_bytes, g->valid_raw, g->n, g->in_deg,
                          g->out_deg, g->rec, g->presence, g->off_table, g->k_pad, g->tile_e, g->tile_m, g->sizes);
 }
 
@@ -1028,7 +1049,7 @@ __global__ __launch_bounds__(kBlock) void k_seg_degree(const SegBuild *__restric
                                                        const SegTile *__restrict__ tiles) {
     const_ptr<SegTile> t = to_const(tiles) + blockIdx.x;
     const_ptr<SegBuild> g = to_const(segs) + t->seg;
-    degree_slots<W, BUF>(g->sp, g->sl, t->tile, g->fit, g->fit_bytes, g->valid_raw, g->n, g->in_deg, g->out_deg,
+    degree_slots<W, BUF>(g->sl, t->tile, g->fit, g->fit_bytes, g->valid_raw, g->n, g->in_deg, g->out_deg,
                          g->rec, g->presence, g->off_table, g->k_pad, g->tile_e, g->tile_m, g->sizes);
 }
 
