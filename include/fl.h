@@ -315,10 +315,11 @@ fl_status fl_analyze_noalloc(fl_ctx *ctx, const fl_space *space, const float *d_
  * segmented launch over the tiles of all running members (one for the
  * slot-sweep members, one for the binned members), followed by one launch
  * that finishes the step of every member.  Each member keeps its own damping,
- * tolerance, iteration count and stop flag, and its results equal those of fl_execute with the slot sweep
- * (row_mapping FL_ROWS_SLOTS, flags FL_STEP_SEPARATE) bit for bit, whatever
- * else runs in the batch.  A batch ignores FL_STEP_SEPARATE in the
- * parameters: its members always take a step kernel per sweep.
+ * tolerance, iteration count and stop flag, and its results equal those of
+ * fl_execute with the slot sweep (row_mapping FL_ROWS_SLOTS, flags
+ * FL_STEP_SEPARATE) bit for bit, whatever else runs in the batch.  A batch
+ * ignores FL_STEP_SEPARATE in the parameters: its members always take a step
+ * kernel per sweep.
  * Members join (fl_batch_add) and leave (fl_batch_collect) between steps.
  * A member reads its plan's FFG and keeps its own iterate vectors (taken
  * from the context's device cache at fl_batch_add, returned when it leaves),

@@ -561,16 +561,16 @@ __device__ __forceinline__ void set_bits(uint64_t (&m)[W], int32_t lo, int32_t h
 // no comparison below counts).
 // SL is a SlotTable, either a kernel argument or an entry of a segment table
 // in the constant address space (scalar loads either way).
-// What bounds it is a wave's serial chain, at eight waves per SIMD, with the
-// texture unit's gathers (116 k of 160 k cycles at the large workload) next.
-// Half of the chain was not the gathers: the digits read each parameter's
-// runs as 16-bit members, which no scalar load takes, so three vector loads
-// waited for one after the other per parameter (now one scalar load of a
-// SlotParam, 82 -> 72 us at 1.5 M nodes and 86 slots, 62 -> 50 at 20 slots),
-// and eleven reductions went through LDS lane exchanges (wave_reduce and one
-// barrier, 72 -> 68 and 50 -> 46).  No gain: the offsets in wide scalar loads
-// ahead of the gathers, and the existence masks from a table in LDS or from
-// shifts of the uniform runs (fewer instructions, same time).
+// What bounds it is instruction issue (38 M VALU, 149 k per CU in 166 k cycles
+// at the large workload; the texture unit is busy for 91 k of them).  Before,
+// waves waited in a serial chain beside the gathers: the digits read each
+// parameter's runs as 16-bit members, which no scalar load takes, so up to
+// three vector loads followed one another per parameter (now one scalar load
+// of a SlotParam: 82 -> 72 us at 1.5 M nodes and 86 slots, 62 -> 50 at 20
+// slots), and eleven reductions went through LDS lane exchanges (wave_reduce
+// and one barrier: 72 -> 68 and 50 -> 46).  No gain: the offsets in wide
+// scalar loads ahead of the gathers, and the existence masks from a table in
+// LDS or from shifts of the uniform runs.
 template <int W, bool BUF, class SL>
 __device__ __forceinline__ void degree_slots(const SL &sl, int32_t tile,
                                              const float *__restrict__ fit, int32_t fit_bytes,
