@@ -1834,10 +1834,12 @@ struct PanelRows {
 
 // Rows of 64 lanes, kLongRows of them at once per wave.  The row bounds are
 // uniform, so a row's terms come through a buffer descriptor that ends with
-// the row: a lane past it reads column 0, whose x it then leaves out.  No lane
-// is masked, so the loads of all the rows are in flight together (under
-// execution masks each row waited for its own: 63 us a sweep; 2 rows at once
-// 62, 3 rows 60, 4 rows 58; more would lower the occupancy below 6).
+// the row: a lane past it reads column 0, whose x it then leaves out.  The
+// whole displacement is in the vector offset, as the scalar one is not part of
+// the bounds check.  No lane is masked, so the loads of all the rows are in
+// flight together (under execution masks each row waited for its own: 63 us a
+// sweep; 2 rows at once 62, 3 rows 60, 4 rows 58; more would lower the
+// occupancy below 6).
 constexpr int kLongRows = 4;
 __device__ __forceinline__ void panel_sums_long(PanelRows &p, const int32_t *__restrict__ col_idx,
                                                 const float *__restrict__ x, int32_t count) {
@@ -1857,7 +1859,7 @@ __device__ __forceinline__ void panel_sums_long(PanelRows &p, const int32_t *__r
             cr[q] = __builtin_amdgcn_make_buffer_rsrc((void *)(col_idx + b), (short)0, 4 * n[q], 0x00020000);
 #pragma unroll
             for (int u = 0; u < 2; ++u)
-                c[q][u] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(cr[q], 4 * lane, 256 * u, 0);
+                c[q][u] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(cr[q], 4 * (lane + 64 * u), 0, 0);
         }
 #pragma unroll
         for (int q = 0; q < R; ++q)
@@ -1874,7 +1876,7 @@ __device__ __forceinline__ void panel_sums_long(PanelRows &p, const int32_t *__r
             for (int q = 0; q < R; ++q)
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
-                    c[q][u] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(cr[q], 4 * (e + lane), 256 * u, 0);
+                    c[q][u] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(cr[q], 4 * (e + lane + 64 * u), 0, 0);
 #pragma unroll
             for (int q = 0; q < R; ++q)
 #pragma unroll
