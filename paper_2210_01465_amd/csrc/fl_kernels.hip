@@ -1914,9 +1914,14 @@ __device__ __forceinline__ void panel_sums(PanelRows &p, const int32_t *__restri
 
 __global__ __launch_bounds__(kPanelBlock) void k_pr_iter_panels(PrArgs a) {
     __shared__ PanelRows p;
-    __shared__ int32_t sh_stop;
+    __shared__ int32_t sh_done, sh_stop;
     const PrState *st = a.st;
-    if (st->done) return;
+    // One reading of the flag for the workgroup: the first workgroup of this
+    // launch may set it meanwhile, and waves that left on readings of their own
+    // would leave the others row bounds that nobody stored.
+    if (threadIdx.x == 0) sh_done = peek_stop(st);
+    __syncthreads();
+    if (sh_done) return;
     const int wg = lag_workgroup<kPanelBlock>(a);
     if (wg < 0) return;
     const float *__restrict__ y_in = a.cur.y_in;
@@ -1948,7 +1953,7 @@ __global__ __launch_bounds__(kPanelBlock) void k_pr_iter_panels(PrArgs a) {
         }
         if (first < 0) break;
         const int t = threadIdx.x;
-        if (t == 0) sh_stop = __hip_atomic_load(const_cast<int32_t *>(&st->done), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (t == 0) sh_stop = peek_stop(st);
         int32_t v = 0, deg = 0;
         float yin = 0.0f, yprev = 0.0f, gv = 0.0f;
         if (t < count) {

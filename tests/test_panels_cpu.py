@@ -71,3 +71,11 @@ def test_long_rows_read_their_own_edges_only(tmp_path):
     lens = [0, 1, 31, 32, 33, 63, 64, 65, 100, 127, 128, 129, 191, 192, 200, 255, 256, 257, 700]
     out = subprocess.run([str(exe)], input=" ".join(map(str, lens)), capture_output=True, text=True, check=True).stdout
     assert [int(line.split()[1]) for line in out.splitlines()] == [0] * len(lens), out
+
+
+def test_the_waves_of_a_workgroup_leave_together():
+    """Every wave stores the bounds of rows that other waves gather, and the
+    first workgroup of a launch may set the stop flag while others start: a
+    wave may not leave, before a barrier, on a reading of its own."""
+    head = function("k_pr_iter_panels").split("__syncthreads")[0]
+    assert "peek_stop" in head and "return" not in head
