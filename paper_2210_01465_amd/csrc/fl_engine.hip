@@ -671,9 +671,8 @@ void build_fill(fl_ctx *ctx, Build &b, bool alone = true) {
     }
     hipStream_t s = ctx->stream;
     if (b.defer && p->sl.words > 0) return;
-    const bool lists = b.slots_only && wants_lists(p);
+    const bool lists = b.slots_only && wants_lists(p) && alloc_lists(ctx, p);   // no room: swept by its records
     hipError_t he = hipSuccess;
-    if (lists && !alloc_lists(ctx, p)) return build_fail(b, FL_ENOMEM, "device allocation failed");
     if (b.slots_only && !lists)
         he = fl::launch_fill_minima(p->out_deg, (int32_t)p->n, b.tile_moff, p->minima, s);
     else
@@ -851,12 +850,16 @@ fl_status resolve_params(fl_ctx *ctx, const fl_plan *p, const fl_params *prm, Re
     return FL_OK;
 }
 
-// The lists of a kept plan, made from its CSR by its first execute.
+// The lists of a plan that is swept by them, made from its CSR by its first
+// execute; none if there is no room for them or the plan was built without a
+// CSR (it then keeps to its records).
 fl_status ensure_lists(fl_ctx *ctx, fl_plan *p) {
-    if (p->lists.quad) return FL_OK;
-    if (!alloc_lists(ctx, p)) return fail(ctx, FL_ENOMEM, "device allocation failed");
-    FL_HIP(fl::launch_make_lists(p->row_ptr, p->col_idx, (int32_t)p->n, p->lists, ctx->stream));
-    return FL_OK;
+    if (p->lists.quad || !p->has_csr || !alloc_lists(ctx, p)) return FL_OK;
+    const hipError_t e = fl::launch_make_lists(p->row_ptr, p->col_idx, (int32_t)p->n, p->lists, ctx->stream);
+    if (e == hipSuccess) return FL_OK;
+    ctx->pool.release(p->lists.quad);
+    p->lists = {};
+    return fail(ctx, FL_EHIP, "in-edge lists: %s", hipGetErrorString(e));
 }
 
 // y, x (x in raw-index space for the slot sweep) and the state of a plan;
@@ -938,9 +941,11 @@ fl_status prepare_pr(fl_ctx *ctx, fl_plan *p, const Resolved &r, int lanes, PrAr
     }
     st = ensure_pr_buffers(ctx, p, kind == fl::kSweepSlots, r.lag);
     if (st != FL_OK) return st;
-    if (kind == fl::kSweepSlots && wants_lists(p) && (p->has_csr || p->lists.quad)) {
+    if (kind == fl::kSweepSlots && wants_lists(p)) {
         st = ensure_lists(ctx, p);
         if (st != FL_OK) return st;
+    }
+    if (kind == fl::kSweepSlots && p->lists.quad) {
         kind = a.kind = fl::kSweepLists;
         a.lists = p->lists;
         // a space that leaves CUs idle spreads its waves over more of them

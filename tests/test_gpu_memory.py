@@ -1,0 +1,50 @@
+"""Device memory that runs out: what the engine can do without it still runs,
+and what fails leaves nothing behind that a later call would trip over."""
+import failing_malloc
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+COMMON = r"""
+import numpy as np, torch
+from paper_2210_01465_amd import _abi, api
+def fitness(radix, excluded, seed=0):
+    rng = np.random.default_rng([31, seed])
+    f = np.exp(0.3 * rng.standard_normal(int(np.prod(radix)))).astype(np.float32)
+    f[rng.random(f.size) < excluded] = np.nan
+    f[-1] = 1.0
+    return torch.from_numpy(f).cuda()
+def close(a, b, iterations):   # each sweep rounds a rank of sum 1 to 2^-24, on either side
+    return float((a - b).abs().sum()) <= 2 * (iterations + 1) * 2.0 ** -24
+"""
+
+
+def test_without_room_for_the_lists():
+    """The in-edge lists are by far the largest buffer here; without them a
+    kept plan and a one-shot analysis run by the slot records."""
+    failing_malloc.run(COMMON + r"""
+radix = (9, 8, 6, 5, 4, 4, 3, 3)
+fit = fitness(radix, 0.62)
+def runs(ctx):
+    plan = api.plan_create(ctx, radix, fit)
+    out = [api.execute(plan, separate_step=sep) for sep in (True, False)]
+    again = api.execute(plan)
+    one = api.analyze(radix, fit, ctx=ctx)
+    plan.close()
+    return out + [again, (one.pagerank, one.minima, one.info)]
+with api.Context(0) as ctx:
+    failing_malloc.fail(0, 0, 16 << 20)
+    want = runs(ctx)
+    assert failing_malloc.calls() >= 1
+with api.Context(0) as ctx:
+    failing_malloc.fail(0, 1 << 30, 16 << 20)
+    got = runs(ctx)
+    assert failing_malloc.calls() >= 4
+    failing_malloc.fail(0, 0)
+    later = runs(ctx)
+for (a, ma, ia), (b, mb, ib), (c, mc, ic) in zip(want, got, later):
+    assert torch.equal(ma, mb) and ia["iterations"] == ib["iterations"] and ia["row_mapping"] == ib["row_mapping"]
+    assert close(a, b, ia["iterations"]) and torch.equal(a, c)
+assert torch.equal(want[0][0], got[0][0])   # a step kernel per sweep: the same sums
+print("ok")
+""")
