@@ -865,20 +865,18 @@ fl_status ensure_lists(fl_ctx *ctx, fl_plan *p) {
 // y, x (x in raw-index space for the slot sweep) and the state of a plan;
 // lag: the third y buffer and g of the lagged step as well.
 fl_status ensure_pr_buffers(fl_ctx *ctx, fl_plan *p, bool slots, bool lag) {
-    if (!p->state) {
-        for (int j = 0; j < 2; ++j) p->y[j] = pool_alloc<float>(ctx, p->n);
-        p->state = pool_alloc<PrState>(ctx, 1);
-        if (!p->y[0] || !p->y[1] || !p->state) return fail(ctx, FL_ENOMEM, "device allocation failed");
-    }
-    if (lag && !p->g) {
-        p->y[2] = pool_alloc<float>(ctx, p->n);
-        p->g = pool_alloc<float>(ctx, p->n);
-        if (!p->y[2] || !p->g) return fail(ctx, FL_ENOMEM, "device allocation failed");
-    }
+    // each by itself: a call that failed half way has left some of them
+    float **vec[] = {&p->y[0], &p->y[1], &p->y[2], &p->g};
+    for (int j = 0; j < (lag ? 4 : 2); ++j)
+        if (!*vec[j] && !(*vec[j] = pool_alloc<float>(ctx, p->n)))
+            return fail(ctx, FL_ENOMEM, "device allocation failed");
+    if (!p->state && !(p->state = pool_alloc<PrState>(ctx, 1)))
+        return fail(ctx, FL_ENOMEM, "device allocation failed");
     // raw-index space, whole 16-byte groups; node ids, and the lists' zero entry
     int64_t x_need = slots ? (p->n_raw + 3) / 4 * 4 : p->n;
     if (wants_lists(p)) x_need = std::max<int64_t>(x_need, p->n + 1);
     if (x_need > p->x_cap) {
+        p->x_cap = 0;
         for (int j = 0; j < 2; ++j) {
             ctx->pool.release(p->x[j]);
             p->x[j] = pool_alloc<float>(ctx, x_need);

@@ -48,3 +48,52 @@ for (a, ma, ia), (b, mb, ib), (c, mc, ic) in zip(want, got, later):
 assert torch.equal(want[0][0], got[0][0])   # a step kernel per sweep: the same sums
 print("ok")
 """)
+
+
+@pytest.mark.parametrize("radix", [(6, 5, 4, 3), (130,), (9, 8, 7, 6, 5)])
+def test_every_allocation_of_a_kept_plan_may_fail(radix):
+    """Whichever allocation fails, a call either gives its result or reports
+    that memory ran out, and the same plan then gives its results."""
+    failing_malloc.run(COMMON + f"radix = {radix!r}\n" + r"""
+fit = fitness(radix, 0.1)
+calls = [dict(separate_step=True), {}, dict(exact=True), dict(row_mapping=1), dict(row_mapping=-2),
+         dict(row_mapping=-2, separate_step=True)]
+def go(plan, kw):
+    pr, mins, info = api.execute(plan, **kw)
+    return pr, mins[:plan.n_minima], info["iterations"]
+def same(x, y):
+    return torch.equal(x[0], y[0]) and torch.equal(x[1], y[1]) and x[2] == y[2]
+def create(ctx):
+    return api.plan_create(ctx, radix, fit)
+with api.Context(0) as ctx:
+    failing_malloc.fail(0, 0)
+    plan = create(ctx)
+    want = [go(plan, kw) for kw in calls]
+    total = failing_malloc.calls()
+    plan.close()
+print(total, "allocations", flush=True)
+failed = 0
+for k in range(total):
+    with api.Context(0) as ctx:
+        plan = None
+        failing_malloc.fail(k, 2)   # the engine asks twice, after it has given back what it holds unused
+        try:
+            plan = create(ctx)
+        except api.FLError as e:
+            assert e.status == _abi.FL_ENOMEM, (k, e)
+            failed += 1
+        if plan is not None:
+            for kw, w in zip(calls, want):
+                try:
+                    r = go(plan, kw)
+                    assert w[2] == r[2] and torch.equal(w[1], r[1]) and close(w[0], r[0], w[2]), (k, kw)
+                except api.FLError as e:
+                    assert e.status == _abi.FL_ENOMEM, (k, kw, e)
+                    failed += 1
+        failing_malloc.fail(0, 0)
+        plan = plan or create(ctx)
+        assert all(same(go(plan, kw), w) for kw, w in zip(calls, want)), k
+        plan.close()
+assert failed >= total // 2, failed
+print("ok")
+""")
