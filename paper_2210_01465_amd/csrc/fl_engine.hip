@@ -415,9 +415,12 @@ uint64_t shape_key(const fl_plan *p) {
 }
 
 // Layout a plan runs in: the one asked for, else the one tuned for its shape
-// class, else the default.
+// class, else the default.  A plan built without a CSR (for a batch, whose
+// members run by slots where a lone space may have a tuned layout) has its
+// records only.
 int layout_of(const fl_ctx *ctx, const fl_plan *p, const fl_params *prm) {
     if (prm->row_mapping != 0) return prm->row_mapping;
+    if (!p->has_csr) return FL_ROWS_SLOTS;
     const auto hit = ctx->tuned.find(shape_key(p));
     if (hit != ctx->tuned.end()) return hit->second;
     return p->sl.words > 0 ? FL_ROWS_SLOTS : FL_ROWS_BINNED;

@@ -97,3 +97,35 @@ for k in range(total):
 assert failed >= total // 2, failed
 print("ok")
 """)
+
+
+def test_a_batch_member_without_room_runs_alone():
+    """A space that cannot join the batch for want of memory runs by itself,
+    also where its shape class has a tuned layout of the CSR, which a space
+    built for the batch does not have."""
+    out = failing_malloc.run(COMMON + r"""
+def batch(radix, first, count):
+    # None where the tuner took another layout, else the number of allocations
+    with api.Context(0) as ctx:
+        plan = api.plan_create(ctx, radix, fitness(radix, 0.0))
+        if api.tune(plan, sweeps=20)["best"] <= 0:   # (the plan stays: its memory is not for the batch)
+            return None
+        failing_malloc.fail(first, count)
+        try:
+            for r in api.analyze_batch([radix] * 3, [fitness(radix, 0.0, j) for j in range(3)], ctx=ctx):
+                assert r.info["iterations"] > 0 and r.pagerank.numel() == plan.n_valid, (first, r.info)
+        except api.FLError as e:   # (the build's own tables report a failed call of the runtime)
+            assert e.status in (_abi.FL_ENOMEM, _abi.FL_EHIP), (first, e)
+        seen = failing_malloc.calls()
+        failing_malloc.fail(0, 0)
+        plan.close()
+        return seen
+for radix in ((129,), (100,), (120, 2), (40, 20), (12, 11, 10)):
+    total = batch(radix, 0, 0)
+    print(radix, total, flush=True)
+    if total is not None:
+        print("tried", sum(batch(radix, first, 2) is not None for first in range(total)))
+        break
+""")
+    if "tried" not in out:
+        pytest.skip("no space here is fastest by a lanes-per-row layout")
