@@ -84,8 +84,9 @@ typedef struct {
  *             FL_ROWS_BINNED = the CSR with rows binned by in-degree into
  *             8 buckets (0; [2^(b-1), 2^b) for b = 1..6; 64 and more), each
  *             bucket with its own lanes per row and rows per tile (the
- *             mapping fl_tune chose for the plan's shape class, else about a
- *             quarter of the bucket's largest in-degree in lanes);
+ *             mapping fl_tune chose for the plan's shape class and the kind
+ *             of step, else about a quarter of the bucket's largest in-degree
+ *             in lanes);
  *             1, 2, 4, 8, 16, 32 or 64 = that many lanes per row over the
  *             CSR.  Every layout sums a row's terms in ascending source
  *             order (one lane per row: sequentially; several: lane partial
@@ -224,7 +225,10 @@ fl_status fl_plan_export(fl_ctx *ctx, const fl_plan *plan, int32_t *d_valid_raw,
  * time `sweeps` binned sweeps over that bucket's rows alone for every lanes
  * per row L in 1, 2, ..., up to the bucket's largest in-degree (64 at most)
  * and every tile of T = 1 or 4 blocks of 256 / L rows, and keep the fastest
- * (L, T) of each bucket as the shape class's bucket mapping.  Then time every
+ * (L, T) of each bucket as the shape class's mapping for sweeps with a step
+ * kernel and batch members.  Without FL_STEP_SEPARATE the sweeps of the lagged
+ * step, whose panels of rows follow L alone, are timed as well and give that
+ * step a mapping of its own (T = 1).  Then time every
  * sweep layout the plan allows (the slot sweep, the CSR sweep with 1, 2, 4,
  * 8, 16, 32, 64 lanes per row, the binned sweep with that mapping) for
  * `sweeps` forced power-iteration sweeps each (HIP events, after one warm-up
@@ -240,7 +244,8 @@ fl_status fl_tune(fl_ctx *ctx, fl_plan *plan, const fl_params *params, int32_t s
                   double *us_per_sweep);
 
 /* The in-degree bucket mapping the context holds for the plan's shape class
- * (tuned by fl_tune, else the default; see FL_ROWS_BINNED) and the plan's
+ * (that of the lagged step if fl_tune chose one, else that of sweeps with a
+ * step kernel, else the default; see FL_ROWS_BINNED) and the plan's
  * rows per bucket.  lanes, blocks (int32[8]) and rows (int64[8]) are host
  * arrays, any may be NULL.  Synchronises the stream when rows is given. */
 fl_status fl_bucket_map(fl_ctx *ctx, const fl_plan *plan, int32_t *lanes, int32_t *blocks, int64_t *rows);

@@ -147,7 +147,9 @@ struct fl_ctx {
     std::string err;
     DevicePool pool;
     std::map<uint64_t, int> tuned;  // shape class -> sweep layout chosen by fl_tune
-    std::map<uint64_t, uint64_t> tuned_map;  // shape class -> in-degree bucket mapping chosen by fl_tune
+    // shape class -> in-degree bucket mappings chosen by fl_tune: for sweeps by
+    // tiles (step kernel, batch members) and by panels (lagged step)
+    std::map<uint64_t, uint64_t> tuned_tiles, tuned_panels;
     char *h_page = nullptr;         // one pinned page that holds the pinned words below
     int32_t *h_bins = nullptr;      // pinned: bucket classes out, class sizes back
     int32_t profile_every = 0;      // bracket every n-th sweep kernel with events (fl_profile), 0 = off
@@ -195,13 +197,16 @@ struct fl_plan {
     double *partials = nullptr;
     PrState *state = nullptr;
     int pr_grid = 0;
-    // rows binned by in-degree (binned sweep): node ids grouped by class,
-    // the classes, and the bucket mapping they were built for
-    int32_t *bin_rows = nullptr;
-    fl::BinTable bins{};
-    uint64_t bin_map = 0;
-    bool have_bins = false;
-    int32_t bin_users = 0;      // batch members sweeping these bins (no rebinning meanwhile)
+    // rows binned by in-degree (binned sweep): node ids grouped by class, the
+    // classes, and the bucket mapping they were built for; one set for sweeps
+    // by tiles, one for sweeps by panels where that mapping is another
+    struct Bins {
+        int32_t *rows = nullptr;
+        fl::BinTable table{};
+        uint64_t map = 0;
+        bool have = false;
+        int32_t users = 0;      // batch members sweeping these bins (no rebinning meanwhile)
+    } tile_bins, panel_bins;
     int32_t *d_off = nullptr;   // 2 k_pad entries in device memory, read by the slot sweep:
                                 // raw-index offsets, then byte offsets from the most negative
                                 // (written by the degree kernel)
@@ -281,8 +286,8 @@ void release_plan_buffers(fl_plan *p) {
     DevicePool &pool = p->ctx->pool;
     void *bufs[] = {p->valid_raw, p->out_deg, p->row_ptr, p->col_idx, p->minima,  p->fit_c,
                     p->rec,       p->presence, p->y[0], p->y[1],      p->y[2],     p->x[0],
-                    p->x[1],      p->g,       p->partials, p->state,  p->d_off,    p->bin_rows,
-                    p->lists.quad};
+                    p->x[1],      p->g,       p->partials, p->state,  p->d_off,    p->tile_bins.rows,
+                    p->panel_bins.rows, p->lists.quad};
     for (void *b : bufs) pool.release(b);
 }
 
@@ -733,7 +738,12 @@ uint64_t default_bin_map() {
     }
     return m;
 }
-uint64_t bin_map_for(const fl_ctx *ctx, uint64_t shape);
+// The mapping of a shape class for sweeps by panels (lagged step) or by tiles.
+uint64_t bin_map_for(const fl_ctx *ctx, uint64_t shape, bool panels) {
+    const auto &tuned = panels ? ctx->tuned_panels : ctx->tuned_tiles;
+    const auto it = tuned.find(shape);
+    return it != tuned.end() ? it->second : default_bin_map();
+}
 
 // Classes of a mapping: its distinct (L, T) pairs in ascending order, and the
 // class of every bucket.  Returns the number of classes.
@@ -802,22 +812,27 @@ fl::BinTable bin_table(int n_classes, const int32_t *rows, const int *lanes, con
     return t;
 }
 
-// The plan's rows binned for mapping m (kept while batch members sweep them).
-fl_status ensure_binned(fl_ctx *ctx, fl_plan *p, uint64_t m) {
-    if (p->have_bins && (p->bin_map == m || p->bin_users > 0)) return FL_OK;
+// The plan's rows binned with its shape class's mapping for sweeps by panels
+// or by tiles, in *out (not binned anew while batch members sweep them).
+fl_status ensure_binned(fl_ctx *ctx, fl_plan *p, bool panels, const fl_plan::Bins **out = nullptr) {
+    const uint64_t m = bin_map_for(ctx, shape_key(p), panels);
+    const bool shared = panels && p->tile_bins.have && p->tile_bins.map == m;
+    fl_plan::Bins &b = panels && !shared ? p->panel_bins : p->tile_bins;
+    if (out) *out = &b;
+    if (b.have && (b.map == m || b.users > 0)) return FL_OK;
     int8_t class_of[fl::kBuckets];
     int lanes[fl::kBuckets], blocks[fl::kBuckets];
     const int nc = bin_classes(m, class_of, lanes, blocks);
-    if (!p->bin_rows) {
-        p->bin_rows = pool_alloc<int32_t>(ctx, p->n);
-        if (!p->bin_rows) return fail(ctx, FL_ENOMEM, "device allocation failed");
+    if (!b.rows) {
+        b.rows = pool_alloc<int32_t>(ctx, p->n);
+        if (!b.rows) return fail(ctx, FL_ENOMEM, "device allocation failed");
     }
     int32_t sizes[fl::kBuckets];
-    const fl_status st = bin_rows_into(ctx, p->row_ptr, p->n, class_of, p->bin_rows, sizes);
+    const fl_status st = bin_rows_into(ctx, p->row_ptr, p->n, class_of, b.rows, sizes);
     if (st != FL_OK) return st;
-    p->bins = bin_table(nc, sizes, lanes, blocks);
-    p->bin_map = m;
-    p->have_bins = true;
+    b.table = bin_table(nc, sizes, lanes, blocks);
+    b.map = m;
+    b.have = true;
     return FL_OK;
 }
 
@@ -917,11 +932,6 @@ void fill_summary(const fl_plan *p, const PrState &hs, int lanes, fl_status stat
     out->score = hs.score_den > 0.0 ? hs.score_num / hs.score_den : 0.0;
 }
 
-uint64_t bin_map_for(const fl_ctx *ctx, uint64_t shape) {
-    const auto it = ctx->tuned_map.find(shape);
-    return it != ctx->tuned_map.end() ? it->second : default_bin_map();
-}
-
 // Grid, buffers and arguments of the power iteration of plan p in layout
 // `lanes` (FL_ROWS_SLOTS or CSR lanes per row).
 fl_status prepare_pr(fl_ctx *ctx, fl_plan *p, const Resolved &r, int lanes, PrArgs &a, int &grid,
@@ -935,10 +945,11 @@ fl_status prepare_pr(fl_ctx *ctx, fl_plan *p, const Resolved &r, int lanes, PrAr
     a.block = fl::kBlock;
     a.lag = r.lag ? 1 : 0;   // the occupancy query asks for the kernel that will run
     if (kind == fl::kSweepBinned) {
-        const fl_status bst = ensure_binned(ctx, p, bin_map_for(ctx, shape_key(p)));
+        const fl_plan::Bins *b = nullptr;
+        const fl_status bst = ensure_binned(ctx, p, r.lag, &b);
         if (bst != FL_OK) return bst;
-        a.bin_rows = p->bin_rows;
-        a.bins = p->bins;
+        a.bin_rows = b->rows;
+        a.bins = b->table;
     }
     st = ensure_pr_buffers(ctx, p, kind == fl::kSweepSlots, r.lag);
     if (st != FL_OK) return st;
@@ -965,14 +976,14 @@ fl_status prepare_pr(fl_ctx *ctx, fl_plan *p, const Resolved &r, int lanes, PrAr
                                 : kind == fl::kSweepBinned                         ? 1
                                                                                    : fl::kBlock / lanes;
     const int64_t groups = kind == fl::kSweepBinned
-                               ? std::max<int64_t>(r.lag ? fl::bin_panels(p->bins) : p->bins.tiles, 1)
+                               ? std::max<int64_t>(r.lag ? fl::bin_panels(a.bins) : a.bins.tiles, 1)
                                : (p->n + rows_per_wg - 1) / rows_per_wg;
     grid = (int)std::min<int64_t>(resident, (groups + fl::kXcds - 1) / fl::kXcds * fl::kXcds);
     // partial sums: one triple per tile (init, slot sweep) or per workgroup
     // (CSR sweep, lagged step: two buffers of them)
     const int32_t n_tiles = tiles_of(p);
     init_grid = (int)std::min<int64_t>(n_tiles, (int64_t)ctx->num_cus * 4);
-    st = ensure_partials(ctx, p, std::max<int64_t>(std::max<int64_t>(2 * (int64_t)grid, n_tiles), p->have_bins ? p->bins.tiles : 0));
+    st = ensure_partials(ctx, p, std::max<int64_t>({2 * (int64_t)grid, n_tiles, a.bins.tiles}));
     if (st != FL_OK) return st;
     a.row_ptr = p->row_ptr;
     a.col_idx = p->col_idx;
@@ -1022,7 +1033,7 @@ struct fl_batch {
         int phase = 0;    // 0 waiting for initialisation, 1 running, 2 finished
         fl_summary sum{};
         bool binned = false;  // binned sweep over the CSR (else the slot sweep)
-        bool holds_bins = false;  // counted in plan->bin_users
+        bool holds_bins = false;  // counted in plan->tile_bins.users
         // the member's own iterate: y (node ids), x (raw indices; node ids
         // when binned), per-tile partial sums and state, from the context's pool
         float *y[2] = {}, *x[2] = {};
@@ -1082,12 +1093,12 @@ namespace {
 // Tiles a member needs in the batch's lists: node tiles (initial iterate,
 // output) and, when binned, the tiles of its bin table (sweeps).
 int64_t member_tiles(const fl_batch::Member &m) {
-    return std::max<int64_t>(tiles_of(m.plan), m.binned ? m.plan->bins.tiles : 0);
+    return std::max<int64_t>(tiles_of(m.plan), m.binned ? m.plan->tile_bins.table.tiles : 0);
 }
 
 void member_release(fl_ctx *ctx, fl_batch::Member &m) {
     if (m.holds_bins) {
-        m.plan->bin_users -= 1;
+        m.plan->tile_bins.users -= 1;
         m.holds_bins = false;
     }
     for (int j = 0; j < 2; ++j) {
@@ -1106,7 +1117,7 @@ fl_status member_alloc(fl_ctx *ctx, const fl_plan *p, fl_batch::Member &m) {
     const int64_t nx = m.binned ? p->n : (p->n_raw + 3) / 4 * 4;
     Carve c;
     c.add(m.y[0], p->n).add(m.y[1], p->n).add(m.x[0], nx).add(m.x[1], nx);
-    c.add(m.partials, 3 * std::max<int64_t>(tiles_of(p), m.binned ? p->bins.tiles : 0)).add(m.state, 1).take(ctx);
+    c.add(m.partials, 3 * std::max<int64_t>(tiles_of(p), m.binned ? p->tile_bins.table.tiles : 0)).add(m.state, 1).take(ctx);
     if (!m.y[0] || !m.y[1] || !m.x[0] || !m.x[1] || !m.partials || !m.state) {
         member_release(ctx, m);
         return fail(ctx, FL_ENOMEM, "device allocation failed");
@@ -1300,7 +1311,7 @@ fl_status fl_plan_create(fl_ctx *ctx, const fl_space *space, const float *d_fitn
         // no slot records: the binned sweep is this plan's layout, so its rows
         // are binned now (a plan may join a batch of another context, which
         // must not allocate from this one)
-        const fl_status bst = ensure_binned(ctx, b.p, bin_map_for(ctx, shape_key(b.p)));
+        const fl_status bst = ensure_binned(ctx, b.p, false);
         if (bst != FL_OK) {
             const std::string msg = ctx->err;
             build_abort(ctx, b);
@@ -1713,10 +1724,13 @@ fl_status bucket_rows(fl_ctx *ctx, const fl_plan *p, int32_t *rows, int32_t *siz
 // The per-bucket part of the autotuner: for every non-empty in-degree bucket,
 // time `sweeps` binned sweeps over that bucket's rows alone for every lanes
 // per row L up to the bucket's largest in-degree (rounded up to a power of
-// two) and T in {1, 4} blocks per tile; *map receives the fastest (L, T) of
-// each bucket (the default for empty buckets).
-fl_status tune_buckets(fl_ctx *ctx, fl_plan *p, const Resolved &r, int32_t sweeps, uint64_t *map) {
+// two); *map receives the fastest of each bucket (the default for empty
+// buckets).  By tiles (with a step kernel elsewhere) every L is timed with T in
+// {1, 4} blocks per tile; by panels, whose size follows L, T stays 1, so that
+// buckets of equal L are one class.
+fl_status tune_buckets(fl_ctx *ctx, fl_plan *p, Resolved r, bool panels, int32_t sweeps, uint64_t *map) {
     hipStream_t s = ctx->stream;
+    r.lag = panels;
     int32_t *rows = pool_alloc<int32_t>(ctx, p->n);
     if (!rows) return fail(ctx, FL_ENOMEM, "device allocation failed");
     int32_t sizes[fl::kBuckets];
@@ -1724,21 +1738,23 @@ fl_status tune_buckets(fl_ctx *ctx, fl_plan *p, const Resolved &r, int32_t sweep
     PrArgs a;
     int grid = 0, init_grid = 0;
     if (st == FL_OK) st = prepare_pr(ctx, p, r, FL_ROWS_BINNED, a, grid, init_grid);
-    // partial triples of the largest candidate table (64 lanes, one block)
-    if (st == FL_OK) st = ensure_partials(ctx, p, p->n / 4 + fl::kBuckets + 1);
     int per_cu = 0;
-    if (st == FL_OK && fl::pr_binned_blocks_per_cu(&per_cu) != hipSuccess) st = fail(ctx, FL_EHIP, "occupancy query");
+    if (st == FL_OK && fl::pr_binned_blocks_per_cu(&per_cu, panels) != hipSuccess)
+        st = fail(ctx, FL_EHIP, "occupancy query");
+    const int64_t resident =
+        std::max<int64_t>(fl::kXcds, (int64_t)std::max(per_cu, 1) * ctx->num_cus / fl::kXcds * fl::kXcds);
+    // partial triples: one per tile of the largest candidate table (64 lanes,
+    // one block), or two buffers of one per workgroup
+    if (st == FL_OK) st = ensure_partials(ctx, p, panels ? 2 * resident : p->n / 4 + fl::kBuckets + 1);
     uint64_t m = default_bin_map();
     if (st == FL_OK) {
         a.partials = p->partials;
-        a.bin_rows = rows;
-        // one bucket's rows at a time, with per-tile partial sums (sized
-        // above): the lagged step's per-workgroup buffers follow the plan's
-        // grid, not these launches'
-        a.lag = 0;
-        hipError_t e = hipMemsetAsync(p->state, 0, sizeof(PrState), s);
+        hipError_t e = panels ? hipSuccess : hipMemsetAsync(p->state, 0, sizeof(PrState), s);
         if (e == hipSuccess) e = fl::launch_pr_init(a, init_grid, s);
-        const int64_t resident = (int64_t)std::max(per_cu, 1) * ctx->num_cus / fl::kXcds * fl::kXcds;
+        // by panels: the first sweep, over all rows, leaves the vectors whole
+        // that the timed ones read
+        if (e == hipSuccess && panels) e = fl::launch_pr_sweep_binned(a, a.bins, grid, s);
+        a.bin_rows = rows;
         int32_t begin = 0;
         for (int b = 0; b < fl::kBuckets && e == hipSuccess; ++b) {
             if (sizes[b] == 0) continue;
@@ -1746,7 +1762,7 @@ fl_status tune_buckets(fl_ctx *ctx, fl_plan *p, const Resolved &r, int32_t sweep
             while (lmax < 64 && lmax < bucket_hi(b)) lmax <<= 1;
             double best = -1.0;
             for (int l = 1; l <= lmax && e == hipSuccess; l <<= 1)
-                for (int t = 1; t <= 4 && e == hipSuccess; t *= 4) {
+                for (int t = 1; t <= (panels ? 1 : 4) && e == hipSuccess; t *= 4) {
                     fl::BinTable tb{};
                     tb.n_classes = 1;
                     tb.c[0].row_begin = begin;
@@ -1755,10 +1771,20 @@ fl_status tune_buckets(fl_ctx *ctx, fl_plan *p, const Resolved &r, int32_t sweep
                     tb.c[0].blocks = (int16_t)t;
                     const int32_t per = t * (fl::kBlock / l);
                     tb.tiles = (sizes[b] + per - 1) / per;
-                    const int g = (int)std::min<int64_t>(resident, (tb.tiles + fl::kXcds - 1) / fl::kXcds * fl::kXcds);
-                    e = fl::launch_pr_sweep_binned(a, tb, g, s);   // warm-up
+                    const int32_t groups = panels ? fl::bin_panels(tb) : tb.tiles;
+                    const int g = (int)std::min<int64_t>(resident, (groups + fl::kXcds - 1) / fl::kXcds * fl::kXcds);
+                    a.sweep = 0;
+                    if (panels) {   // the launch's own grid, and a state of its own
+                        a.n_parts = a.part_stride = g;
+                        a.reducer = g < resident ? 1 : 0;
+                        e = fl::launch_pr_init(a, init_grid, s);
+                    }
+                    if (e == hipSuccess) e = fl::launch_pr_sweep_binned(a, tb, g, s);   // warm-up
                     if (e == hipSuccess) e = hipEventRecord(p->ev[5], s);
-                    for (int32_t q = 0; q < sweeps && e == hipSuccess; ++q) e = fl::launch_pr_sweep_binned(a, tb, g, s);
+                    for (int32_t q = 0; q < sweeps && e == hipSuccess; ++q) {
+                        a.sweep = q + 1;
+                        e = fl::launch_pr_sweep_binned(a, tb, g, s);
+                    }
                     if (e == hipSuccess) e = hipEventRecord(p->ev[6], s);
                     if (e == hipSuccess) e = hipStreamSynchronize(s);
                     const double us = e == hipSuccess ? 1e3 * elapsed(p->ev[5], p->ev[6]) / sweeps : 0.0;
@@ -1794,11 +1820,18 @@ fl_status fl_tune(fl_ctx *ctx, fl_plan *p, const fl_params *prm, int32_t sweeps,
     FL_HIP(hipSetDevice(ctx->device));
     FL_HIP(ensure_events(p));
     hipStream_t s = ctx->stream;
-    // the bucket mapping first, so that the binned layout below is timed with it
+    // the bucket mappings first, so that the binned layout below is timed with
+    // its own: by tiles always (batch members sweep by them), by panels for the
+    // lagged step
     uint64_t map = 0;
-    st = tune_buckets(ctx, p, r, sweeps, &map);
+    st = tune_buckets(ctx, p, r, false, sweeps, &map);
     if (st != FL_OK) return st;
-    ctx->tuned_map[shape_key(p)] = map;
+    ctx->tuned_tiles[shape_key(p)] = map;
+    if (r.lag) {
+        st = tune_buckets(ctx, p, r, true, sweeps, &map);
+        if (st != FL_OK) return st;
+        ctx->tuned_panels[shape_key(p)] = map;
+    }
     const int layouts[FL_TUNE_LAYOUTS] = {FL_ROWS_SLOTS, 1, 2, 4, 8, 16, 32, 64, FL_ROWS_BINNED};
     double best_us = 0.0;
     *best = 0;
@@ -1839,7 +1872,8 @@ fl_status fl_bucket_map(fl_ctx *ctx, const fl_plan *p, int32_t *lanes, int32_t *
     ctx->err.clear();
     if (!p || p->ctx != ctx) return fail(ctx, FL_EINVAL, "bad plan");
     FL_HIP(hipSetDevice(ctx->device));
-    const uint64_t m = bin_map_for(ctx, shape_key(p));
+    const uint64_t shape = shape_key(p);
+    const uint64_t m = bin_map_for(ctx, shape, ctx->tuned_panels.count(shape) > 0);
     for (int b = 0; b < fl::kBuckets; ++b) {
         if (lanes) lanes[b] = map_lanes(m, b);
         if (blocks) blocks[b] = map_blocks(m, b);
@@ -1960,9 +1994,9 @@ fl_status fl_batch_add(fl_ctx *ctx, fl_batch *b, fl_plan *p, const fl_params *pr
     bool binned = member_binned(ctx, p, prm);
     if (binned) {
         if (p->ctx == ctx) {
-            st = ensure_binned(ctx, p, bin_map_for(ctx, shape_key(p)));
+            st = ensure_binned(ctx, p, false);
             if (st != FL_OK) return st;
-        } else if (!p->have_bins) {
+        } else if (!p->tile_bins.have) {
             if (!slot_ok || is_binned_layout(prm->row_mapping))
                 return fail(ctx, FL_EINVAL, "the plan (of another context) has no binned rows");
             binned = false;
@@ -1978,7 +2012,7 @@ fl_status fl_batch_add(fl_ctx *ctx, fl_batch *b, fl_plan *p, const fl_params *pr
     st = member_alloc(ctx, p, m);
     if (st != FL_OK) return st;
     if (binned) {
-        p->bin_users += 1;
+        p->tile_bins.users += 1;
         m.holds_bins = true;
     }
     m.plan = p;
@@ -2017,12 +2051,12 @@ fl_status fl_batch_add(fl_ctx *ctx, fl_batch *b, fl_plan *p, const fl_params *pr
     bm.n_tiles = tiles_of(p);
     bm.max_iter = r.max_iter;
     bm.xmap = binned ? nullptr : p->valid_raw;
-    bm.n_parts = binned ? p->bins.tiles : tiles_of(p);
+    bm.n_parts = binned ? p->tile_bins.table.tiles : tiles_of(p);
     if (binned) {
         bm.row_ptr = p->row_ptr;
         bm.col_idx = p->col_idx;
-        bm.bin_rows = p->bin_rows;
-        bm.bins = p->bins;
+        bm.bin_rows = p->tile_bins.rows;
+        bm.bins = p->tile_bins.table;
     }
     b->members.push_back(m);
     return FL_OK;
@@ -2045,7 +2079,7 @@ fl_status fl_batch_step(fl_ctx *ctx, fl_batch *b, int32_t sweeps, int32_t *n_run
         int64_t t_join = 0, t_run = 0;
         for (const auto &m : b->members) {
             if (m.phase == 0) t_join += tiles_of(m.plan);
-            if (m.phase <= 1) t_run += std::max<int64_t>(tiles_of(m.plan), m.binned ? m.plan->bins.tiles : 0);
+            if (m.phase <= 1) t_run += std::max<int64_t>(tiles_of(m.plan), m.binned ? m.plan->tile_bins.table.tiles : 0);
         }
         if (t_join > tc || t_run > tc || (int64_t)b->members.size() > b->capacity)
             return fail(ctx, FL_EINVAL, "batch tables hold %lld tiles and %d members: %lld joining tiles, %lld "
@@ -2076,7 +2110,7 @@ fl_status fl_batch_step(fl_ctx *ctx, fl_batch *b, int32_t sweeps, int32_t *n_run
         for (auto &m : b->members) {
             if (m.phase != 1 || width(m) != w || small(m)) continue;
             i_run[n_run++] = m.slot;
-            const int32_t sweep_tiles = m.binned ? m.plan->bins.tiles : tiles_of(m.plan);
+            const int32_t sweep_tiles = m.binned ? m.plan->tile_bins.table.tiles : tiles_of(m.plan);
             for (int32_t t = 0; t < sweep_tiles; ++t) t_sweep[nt++] = {m.slot, t};
         }
     }

@@ -1,0 +1,41 @@
+"""The tuner's bucket mappings: sweeps by panels (lagged step) and by tiles
+(step kernel, batch members) are other kernels, and each has a mapping chosen
+by its own times."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("radix,excluded", [((700,), 0.0), ((64, 70, 5), 0.1), ((200, 3), 0.0), ((6, 5, 4, 3), 0.2)])
+def test_each_kind_of_sweep_has_its_mapping(radix, excluded):
+    import torch
+    from paper_2210_01465_amd import api
+    rng = np.random.default_rng([37, len(radix)])
+    f = np.exp(0.3 * rng.standard_normal(int(np.prod(radix)))).astype(np.float32)
+    f[rng.random(f.size) < excluded] = np.nan
+    print(f"[case] tuned panels {radix}", flush=True)
+    with api.Context(0) as ctx:
+        plan = api.plan_create(ctx, radix, torch.from_numpy(f).cuda(), "hamming")
+        map_ = api.tune(plan, sweeps=3)["buckets"]
+        # a panel's rows follow its lanes alone: no classes that differ in T
+        assert {b["blocks"] for b in map_.values()} == {1}
+        ref = oracle.analyze(radix, f, oracle.HAMMING, 0.85, 0.05, tol=1e-12)
+        runs = [api.execute(plan, 0.85, 0.05, row_mapping=-2, separate_step=sep) for sep in (False, True)] * 2
+        for pr, mins, info in runs:
+            assert info["row_mapping"] == -2 and np.array_equal(mins.cpu().numpy(), ref.graph.minima)
+            assert float(np.abs(pr.cpu().numpy() - ref.pagerank).sum()) <= 1e-5
+        # each kind again after the other: the same bits
+        assert torch.equal(runs[0][0], runs[2][0]) and torch.equal(runs[1][0], runs[3][0])
+        # a batch member sweeps by tiles with the tiles' mapping
+        batch = api.Batch(ctx)
+        batch.add(plan, 0.85, 0.05, row_mapping=-2, tag=1)
+        lagged = api.execute(plan, 0.85, 0.05, row_mapping=-2)[0]   # beside it, with bins of its own
+        while batch.step(16):
+            pass
+        (_, pr, mins, info), = batch.collect()
+        assert torch.equal(pr, runs[1][0]) and torch.equal(lagged, runs[0][0])
+        batch.close()
+        plan.close()
