@@ -710,7 +710,6 @@ void fill_sizes(const fl_plan *p, fl_summary *sizes) {
     sizes->f_opt = (double)p->f_opt;
 }
 
-// Analysis parameters with the defaults applied.
 // ---- rows binned by in-degree ----
 // A bucket mapping: byte b holds log2 of bucket b's lanes per row (bits 0..2)
 // and of its row blocks per tile (bits 3..4).
@@ -812,6 +811,24 @@ fl::BinTable bin_table(int n_classes, const int32_t *rows, const int *lanes, con
     return t;
 }
 
+// Whether a binned sweep with the lagged step goes by panels of rows (else by
+// tiles).  A panel is 128 to 512 rows of one workgroup: the rows must be long
+// enough for the gathers to outweigh its two barriers, and there must be
+// enough panels, of not too many edges each, for the CUs to share.  Of 170
+// spaces of 1 to 4 value lists (35 to 990 000 nodes, 3 to 2 500 edges per
+// node), the 70 on this side take 0.94 to 3.5 times as long by tiles, the
+// others 0.9 to 5.5 times as long by panels.  Per sweep, panels against tiles:
+// 387 k nodes, 28 M edges 72 : 186 us; 140 k, 9.9 M 32 : 65; 52 k, 2.9 M
+// 18.8 : 21.0; 145 k, 4.7 M 20.9 : 21.8; on the other side 167 k, 2.6 M
+// 22.1 : 18.8; 48 k, 4.3 M 30 : 24; 13 k, 10 M 62 : 31; 72 k, 45 M 234 : 205;
+// 5 000, 12 M 145 : 26.
+bool wants_panels(const fl_plan *p) {
+    const int64_t n = p->n, e = p->e;
+    if (e < 16 * n) return false;
+    if (e > 80 * n) return n >= 50000 && e <= n * n / 250;
+    return e >= (e < 32 * n ? int64_t(1) << 22 : int64_t(1) << 21);
+}
+
 // The plan's rows binned with its shape class's mapping for sweeps by panels
 // or by tiles, in *out (not binned anew while batch members sweep them).
 fl_status ensure_binned(fl_ctx *ctx, fl_plan *p, bool panels, const fl_plan::Bins **out = nullptr) {
@@ -836,6 +853,7 @@ fl_status ensure_binned(fl_ctx *ctx, fl_plan *p, bool panels, const fl_plan::Bin
     return FL_OK;
 }
 
+// Analysis parameters with the defaults applied.
 struct Resolved {
     double d, p, tol;
     int32_t max_iter;
@@ -945,8 +963,12 @@ fl_status prepare_pr(fl_ctx *ctx, fl_plan *p, const Resolved &r, int lanes, PrAr
     a.block = fl::kBlock;
     a.lag = r.lag ? 1 : 0;   // the occupancy query asks for the kernel that will run
     if (kind == fl::kSweepBinned) {
+        if (r.lag && wants_panels(p)) {
+            kind = a.kind = fl::kSweepPanels;
+            a.block = fl::kPanelBlock;
+        }
         const fl_plan::Bins *b = nullptr;
-        const fl_status bst = ensure_binned(ctx, p, r.lag, &b);
+        const fl_status bst = ensure_binned(ctx, p, kind == fl::kSweepPanels, &b);
         if (bst != FL_OK) return bst;
         a.bin_rows = b->rows;
         a.bins = b->table;
@@ -973,10 +995,10 @@ fl_status prepare_pr(fl_ctx *ctx, fl_plan *p, const Resolved &r, int lanes, PrAr
     const int64_t resident =
         std::max<int64_t>(fl::kXcds, (int64_t)std::max(per_cu, 1) * ctx->num_cus / fl::kXcds * fl::kXcds);
     const int64_t rows_per_wg = kind == fl::kSweepSlots || kind == fl::kSweepLists ? a.block
-                                : kind == fl::kSweepBinned                         ? 1
+                                : is_binned_layout(lanes)                          ? 1
                                                                                    : fl::kBlock / lanes;
-    const int64_t groups = kind == fl::kSweepBinned
-                               ? std::max<int64_t>(r.lag ? fl::bin_panels(a.bins) : a.bins.tiles, 1)
+    const int64_t groups = is_binned_layout(lanes)
+                               ? std::max<int64_t>(kind == fl::kSweepPanels ? fl::bin_panels(a.bins) : a.bins.tiles, 1)
                                : (p->n + rows_per_wg - 1) / rows_per_wg;
     grid = (int)std::min<int64_t>(resident, (groups + fl::kXcds - 1) / fl::kXcds * fl::kXcds);
     // partial sums: one triple per tile (init, slot sweep) or per workgroup
@@ -1739,7 +1761,7 @@ fl_status tune_buckets(fl_ctx *ctx, fl_plan *p, Resolved r, bool panels, int32_t
     int grid = 0, init_grid = 0;
     if (st == FL_OK) st = prepare_pr(ctx, p, r, FL_ROWS_BINNED, a, grid, init_grid);
     int per_cu = 0;
-    if (st == FL_OK && fl::pr_binned_blocks_per_cu(&per_cu, panels) != hipSuccess)
+    if (st == FL_OK && fl::pr_iter_blocks_per_cu(a, p->sp, p->sl, FL_ROWS_BINNED, &per_cu) != hipSuccess)
         st = fail(ctx, FL_EHIP, "occupancy query");
     const int64_t resident =
         std::max<int64_t>(fl::kXcds, (int64_t)std::max(per_cu, 1) * ctx->num_cus / fl::kXcds * fl::kXcds);
@@ -1821,13 +1843,13 @@ fl_status fl_tune(fl_ctx *ctx, fl_plan *p, const fl_params *prm, int32_t sweeps,
     FL_HIP(ensure_events(p));
     hipStream_t s = ctx->stream;
     // the bucket mappings first, so that the binned layout below is timed with
-    // its own: by tiles always (batch members sweep by them), by panels for the
-    // lagged step
+    // its own: by tiles always (batch members sweep by them), by panels where
+    // the lagged step's sweeps use them
     uint64_t map = 0;
     st = tune_buckets(ctx, p, r, false, sweeps, &map);
     if (st != FL_OK) return st;
     ctx->tuned_tiles[shape_key(p)] = map;
-    if (r.lag) {
+    if (r.lag && wants_panels(p)) {
         st = tune_buckets(ctx, p, r, true, sweeps, &map);
         if (st != FL_OK) return st;
         ctx->tuned_panels[shape_key(p)] = map;
@@ -1872,8 +1894,7 @@ fl_status fl_bucket_map(fl_ctx *ctx, const fl_plan *p, int32_t *lanes, int32_t *
     ctx->err.clear();
     if (!p || p->ctx != ctx) return fail(ctx, FL_EINVAL, "bad plan");
     FL_HIP(hipSetDevice(ctx->device));
-    const uint64_t shape = shape_key(p);
-    const uint64_t m = bin_map_for(ctx, shape, ctx->tuned_panels.count(shape) > 0);
+    const uint64_t m = bin_map_for(ctx, shape_key(p), wants_panels(p));
     for (int b = 0; b < fl::kBuckets; ++b) {
         if (lanes) lanes[b] = map_lanes(m, b);
         if (blocks) blocks[b] = map_blocks(m, b);

@@ -177,7 +177,8 @@ enum SweepKind : int32_t {
     kSweepCsr = 0,    // pull over the CSR, L lanes per row, x indexed by node id
     kSweepSlots = 1,  // pull over the records' in-edge slot bits, x indexed by raw index
     kSweepBinned = 2, // pull over the CSR with rows binned by in-degree, each bin its own lanes per row
-    kSweepLists = 3   // pull over the waves' in-edge lists, x indexed by node id (n + 1 entries, the last 0)
+    kSweepLists = 3,  // pull over the waves' in-edge lists, x indexed by node id (n + 1 entries, the last 0)
+    kSweepPanels = 4  // as kSweepBinned, by panels of rows (lagged step only)
 };
 
 // Rows binned by in-degree: bucket 0 holds in-degree 0, bucket b >= 1 the
@@ -258,7 +259,8 @@ struct PrArgs {
     int32_t sweep;
     int32_t n_parts;
     int32_t part_stride;
-    int32_t block;     // threads per workgroup of the sweep (list sweep: 64 or kBlock; else kBlock)
+    int32_t block;     // threads per workgroup of the sweep (list sweep: 64 or kBlock; panels: kPanelBlock;
+                       // else kBlock)
     int32_t reducer;   // 1: the step has a workgroup of its own (the first of grid + 1)
     int64_t n_sinks;
     uint64_t *progress;   // pinned host word the step reports to (may be null)
@@ -350,7 +352,6 @@ hipError_t launch_bin_rows(const int32_t *row_ptr, int32_t n, const int8_t *clas
 // One binned sweep restricted to the given table (the autotuner times one
 // class at a time this way), without the step kernel.
 hipError_t launch_pr_sweep_binned(const PrArgs &a, const BinTable &t, int grid, hipStream_t stream);
-hipError_t pr_binned_blocks_per_cu(int *blocks, bool lag = false);
 // Panels (one workgroup at a time each) of a lagged binned sweep.
 int32_t bin_panels(const BinTable &t);
 hipError_t launch_batch_sweep_binned(const BatchMember *members, const TileRef *tiles, const int32_t *range_dev,

