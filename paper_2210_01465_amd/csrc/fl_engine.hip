@@ -153,7 +153,7 @@ struct fl_ctx {
     char *h_page = nullptr;         // one pinned page that holds the pinned words below
     int32_t *h_bins = nullptr;      // pinned: bucket classes out, class sizes back
     int32_t profile_every = 0;      // bracket every n-th sweep kernel with events (fl_profile), 0 = off
-    std::vector<hipEvent_t> sweep_ev;  // 2 per launch of the longest chunk so far
+    std::vector<hipEvent_t> sweep_ev;  // pairs of SweepClock, made as they are needed
     BuildSizes *h_sizes = nullptr;  // pinned: written by the build stages, polled by the host
     uint32_t stamp = 0;             // of the last build stage that reports to h_sizes
     PrState *h_state = nullptr;     // pinned
@@ -1347,15 +1347,48 @@ fl_status fl_plan_create(fl_ctx *ctx, const fl_space *space, const float *d_fitn
 
 namespace {
 
-// A pair of events around one sweep (fl_profile): the ctx's j-th pair.
-fl_status sweep_events(fl_ctx *ctx, int j) {
-    while ((int)ctx->sweep_ev.size() < 2 * (j + 1)) {
-        hipEvent_t e;
-        FL_HIP(hipEventCreate(&e));
-        ctx->sweep_ev.push_back(e);
+// Times of single sweeps (fl_profile): every every-th launch between a pair of
+// the context's events, kPairs of them taken in turn.
+struct SweepClock {
+    static constexpr int kPairs = 64;
+    fl_ctx *ctx = nullptr;
+    int32_t every = 0;   // 0: off
+    int64_t recorded = 0, read = 0;
+    double ms = 0.0;
+
+    hipEvent_t *pair(int64_t sample) const { return &ctx->sweep_ev[2 * (sample % kPairs)]; }
+    bool sampled(int64_t launch) const { return every > 0 && launch % every == 0; }
+
+    // Around a sampled launch.  The pair it takes must have been read, or
+    // belong to a sweep that is known to have done its work.
+    fl_status begin(hipStream_t s) {
+        if (recorded - read == kPairs) read_one();
+        while ((int64_t)ctx->sweep_ev.size() < 2 * std::min<int64_t>(recorded + 1, kPairs)) {
+            hipEvent_t e;
+            FL_HIP(hipEventCreate(&e));
+            ctx->sweep_ev.push_back(e);
+        }
+        FL_HIP(hipEventRecord(pair(recorded)[0], s));
+        return FL_OK;
     }
-    return FL_OK;
-}
+    fl_status end(hipStream_t s) {
+        FL_HIP(hipEventRecord(pair(recorded)[1], s));
+        ++recorded;
+        return FL_OK;
+    }
+    // Adds the times of the sampled launches among the first `worked`; those
+    // after them exited at once and are not counted.
+    void collect(int64_t worked) {
+        while (read < recorded && read * every < worked) read_one();
+    }
+
+  private:
+    void read_one() {
+        hipEvent_t *e = pair(read++);
+        (void)hipEventSynchronize(e[1]);
+        ms += elapsed(e[0], e[1]);
+    }
+};
 
 // How the lagged sweeps' host loop stands: what the device last reported.
 struct Progress {
@@ -1385,7 +1418,7 @@ constexpr int kSweepLead = 6;      // launches ahead of the last report: a launc
                                    // the shortest sweep 3, a report 1 to 2
 constexpr int kLastLead = 2;       // near the end
 fl_status run_lagged(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int lanes, int grid, bool exact,
-                     int32_t profile_every, int *launches_out) {
+                     SweepClock &clock, int *launches_out) {
     hipStream_t s = ctx->stream;
     const int64_t limit = (int64_t)r.max_iter + (exact ? 1 : 2);
     __atomic_store_n(ctx->h_progress, uint64_t(0), __ATOMIC_RELEASE);
@@ -1397,15 +1430,14 @@ fl_status run_lagged(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int 
         const bool room = launches < std::min(limit, seen.sweep + ahead);
         if (room) {
             a.sweep = (int32_t)launches;
-            const bool timed_here = profile_every > 0 && launches % profile_every == 0;
-            const int pair = timed_here ? (int)(launches / profile_every) : 0;
-            if (timed_here) {
-                const fl_status st = sweep_events(ctx, pair);
-                if (st != FL_OK) return st;
-                FL_HIP(hipEventRecord(ctx->sweep_ev[2 * pair], s));
-            }
+            // (a pair's last launch lies at least kPairs back, before the one last reported)
+            static_assert(SweepClock::kPairs > kSweepLead, "pairs of events");
+            const bool timed_here = clock.sampled(launches);
+            fl_status st = timed_here ? clock.begin(s) : FL_OK;
+            if (st != FL_OK) return st;
             FL_HIP(fl::launch_pr_sweep(a, p->sl, lanes, grid, s));
-            if (timed_here) FL_HIP(hipEventRecord(ctx->sweep_ev[2 * pair + 1], s));
+            if (timed_here) st = clock.end(s);
+            if (st != FL_OK) return st;
             ++launches;
         }
         read_progress(ctx->h_progress, now);
@@ -1440,25 +1472,23 @@ fl_status run_lagged(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int 
 // chunk length follows the observed residual decay so that few host round
 // trips and few empty launches are needed.
 fl_status run_separate(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int lanes, int grid, bool exact,
-                       int32_t profile_every, int *launches_out) {
+                       SweepClock &clock, int *launches_out) {
     hipStream_t s = ctx->stream;
     PrState *hs = ctx->h_state;
     int launches = 0, chunk = 16;
     for (;;) {
         for (int j = 0; j < chunk; ++j, ++launches) {
-            const bool timed_here = profile_every > 0 && launches % profile_every == 0;
-            const int pair = timed_here ? launches / profile_every : 0;
-            if (timed_here) {
-                const fl_status st = sweep_events(ctx, pair);
-                if (st != FL_OK) return st;
-                FL_HIP(hipEventRecord(ctx->sweep_ev[2 * pair], s));
-            }
+            const bool timed_here = clock.sampled(launches);
+            fl_status st = timed_here ? clock.begin(s) : FL_OK;
+            if (st != FL_OK) return st;
             FL_HIP(fl::launch_pr_sweep(a, p->sl, lanes, grid, s));
-            if (timed_here) FL_HIP(hipEventRecord(ctx->sweep_ev[2 * pair + 1], s));
+            if (timed_here) st = clock.end(s);
+            if (st != FL_OK) return st;
             FL_HIP(fl::launch_pr_step(a, grid, s));
         }
         FL_HIP(hipMemcpyAsync(hs, p->state, sizeof(PrState), hipMemcpyDeviceToHost, s));
         FL_HIP(hipStreamSynchronize(s));
+        clock.collect(hs->worked);
         if (hs->done) break;
         const double rate = (hs->resid_prev > 0.0) ? hs->resid / hs->resid_prev : 1.0;
         if (exact) {
@@ -1496,7 +1526,9 @@ fl_status execute_impl(fl_ctx *ctx, fl_plan *p, const fl_params *prm, double *d_
     if (st != FL_OK) return st;
     a.exact = exact ? 1 : 0;
     const bool timed = !quiet;
-    const int32_t profile_every = quiet ? 0 : ctx->profile_every;
+    SweepClock clock;
+    clock.ctx = ctx;
+    clock.every = quiet ? 0 : ctx->profile_every;
     if (timed) FL_HIP(ensure_events(p));
 
     if (timed) FL_HIP(hipEventRecord(p->ev[2], s));
@@ -1504,7 +1536,7 @@ fl_status execute_impl(fl_ctx *ctx, fl_plan *p, const fl_params *prm, double *d_
     FL_HIP(fl::launch_pr_init(a, init_grid, s));
     if (timed) FL_HIP(hipEventRecord(p->ev[5], s));
     int launches = 0;
-    st = (r.lag ? run_lagged : run_separate)(ctx, p, r, a, lanes, grid, exact, profile_every, &launches);
+    st = (r.lag ? run_lagged : run_separate)(ctx, p, r, a, lanes, grid, exact, clock, &launches);
     if (st != FL_OK) return st;
     if (timed) FL_HIP(hipEventRecord(p->ev[6], s));
     if (timed) FL_HIP(hipEventRecord(p->ev[3], s));
@@ -1516,16 +1548,12 @@ fl_status execute_impl(fl_ctx *ctx, fl_plan *p, const fl_params *prm, double *d_
     FL_HIP(hipMemcpyAsync(hs, p->state, sizeof(PrState), hipMemcpyDeviceToHost, s));
     FL_HIP(hipStreamSynchronize(s));
 
-    double sweep_ms = 0.0;
-    int sampled = 0;
-    if (profile_every > 0)   // launches past the converged iteration exit at once: not counted
-        for (int j = 0; j < launches && j < hs->worked; j += profile_every, ++sampled)
-            sweep_ms += elapsed(ctx->sweep_ev[2 * sampled], ctx->sweep_ev[2 * sampled + 1]);
+    clock.collect(hs->worked);
     p->timing.pagerank_ms = timed ? elapsed(p->ev[2], p->ev[3]) : 0.0;
     p->timing.score_ms = timed ? elapsed(p->ev[3], p->ev[4]) : 0.0;
     p->timing.iterate_ms = timed ? elapsed(p->ev[5], p->ev[6]) : 0.0;
-    p->timing.sweep_ms = sweep_ms;
-    p->timing.sweeps_timed = sampled;
+    p->timing.sweep_ms = clock.ms;
+    p->timing.sweeps_timed = (int32_t)clock.read;
     p->timing.iterations = hs->worked;
     p->timing.launches = launches;
     const fl_status result = hs->done == 1 ? FL_OK : FL_ENOCONV;

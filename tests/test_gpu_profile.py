@@ -1,0 +1,30 @@
+"""Times of single sweeps (fl_profile) over long runs."""
+import failing_malloc
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("separate", [False, True])
+@pytest.mark.parametrize("every", [1, 7])
+def test_long_runs_take_no_more_events(every, separate):
+    """A path of 1 500 nodes settles after as many exact sweeps: each sampled
+    one that did work is counted, and the context keeps no more events than for
+    a short run."""
+    failing_malloc.run(f"every, separate = {every}, {separate}\n" + r"""
+import numpy as np, torch
+from paper_2210_01465_amd import api
+with api.Context(0) as ctx:
+    f = torch.from_numpy(np.arange(1, 1501, dtype=np.float32)).cuda()
+    plan = api.plan_create(ctx, (1500,), f, "adjacent")
+    api.profile(ctx, every)
+    before = failing_malloc.events()
+    for _ in range(2):
+        info = api.execute(plan, 1.0, exact=True, separate_step=separate)[2]
+        t = api.plan_timing(plan)
+        print(info["iterations"], t, failing_malloc.events() - before)
+        assert t["iterations"] >= 1499 and t["sweeps_timed"] == -(-t["iterations"] // every)
+        assert 0.0 < t["sweep_ms"] <= t["pagerank_ms"]
+    assert failing_malloc.events() - before <= 128
+    plan.close()
+""")
