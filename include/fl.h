@@ -144,7 +144,8 @@ typedef struct {
 typedef struct {
     double build_ms;     /* compaction, degree count, scan, CSR fill */
     double pagerank_ms;  /* initialisation + all power iterations, host round trips included */
-    double iterate_ms;   /* device time from the first iteration launch to the last */
+    double iterate_ms;   /* device time of the iteration launches alone (with FL_STEP_SEPARATE: sum over
+                            chunks, without the host round trips between them) */
     double score_ms;     /* output of the ranks, minima and C_p */
     int32_t iterations;  /* iteration kernels that did work */
     int32_t launches;    /* iteration kernels launched (extra ones exit at once) */

@@ -1472,11 +1472,12 @@ fl_status run_lagged(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int 
 // chunk length follows the observed residual decay so that few host round
 // trips and few empty launches are needed.
 fl_status run_separate(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int lanes, int grid, bool exact,
-                       SweepClock &clock, int *launches_out) {
+                       SweepClock &clock, double *iterate_ms, int *launches_out) {
     hipStream_t s = ctx->stream;
     PrState *hs = ctx->h_state;
     int launches = 0, chunk = 16;
     for (;;) {
+        if (iterate_ms) FL_HIP(hipEventRecord(p->ev[5], s));
         for (int j = 0; j < chunk; ++j, ++launches) {
             const bool timed_here = clock.sampled(launches);
             fl_status st = timed_here ? clock.begin(s) : FL_OK;
@@ -1486,8 +1487,10 @@ fl_status run_separate(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, in
             if (st != FL_OK) return st;
             FL_HIP(fl::launch_pr_step(a, grid, s));
         }
+        if (iterate_ms) FL_HIP(hipEventRecord(p->ev[6], s));
         FL_HIP(hipMemcpyAsync(hs, p->state, sizeof(PrState), hipMemcpyDeviceToHost, s));
         FL_HIP(hipStreamSynchronize(s));
+        if (iterate_ms) *iterate_ms += elapsed(p->ev[5], p->ev[6]);
         clock.collect(hs->worked);
         if (hs->done) break;
         const double rate = (hs->resid_prev > 0.0) ? hs->resid / hs->resid_prev : 1.0;
@@ -1534,11 +1537,16 @@ fl_status execute_impl(fl_ctx *ctx, fl_plan *p, const fl_params *prm, double *d_
     if (timed) FL_HIP(hipEventRecord(p->ev[2], s));
     if (!r.lag) FL_HIP(hipMemsetAsync(p->state, 0, sizeof(PrState), s));   // the lagged start writes it whole
     FL_HIP(fl::launch_pr_init(a, init_grid, s));
-    if (timed) FL_HIP(hipEventRecord(p->ev[5], s));
     int launches = 0;
-    st = (r.lag ? run_lagged : run_separate)(ctx, p, r, a, lanes, grid, exact, clock, &launches);
+    double iterate_ms = 0.0;
+    if (r.lag) {   // one uninterrupted run of launches
+        if (timed) FL_HIP(hipEventRecord(p->ev[5], s));
+        st = run_lagged(ctx, p, r, a, lanes, grid, exact, clock, &launches);
+        if (st == FL_OK && timed) FL_HIP(hipEventRecord(p->ev[6], s));
+    } else {
+        st = run_separate(ctx, p, r, a, lanes, grid, exact, clock, timed ? &iterate_ms : nullptr, &launches);
+    }
     if (st != FL_OK) return st;
-    if (timed) FL_HIP(hipEventRecord(p->ev[6], s));
     if (timed) FL_HIP(hipEventRecord(p->ev[3], s));
     FL_HIP(fl::launch_pr_output(a, d_pagerank, p->minima, (int32_t)p->m, d_minima, d_valid_raw, s));
     const double threshold = (1.0 + r.p) * (double)p->f_opt;
@@ -1551,7 +1559,7 @@ fl_status execute_impl(fl_ctx *ctx, fl_plan *p, const fl_params *prm, double *d_
     clock.collect(hs->worked);
     p->timing.pagerank_ms = timed ? elapsed(p->ev[2], p->ev[3]) : 0.0;
     p->timing.score_ms = timed ? elapsed(p->ev[3], p->ev[4]) : 0.0;
-    p->timing.iterate_ms = timed ? elapsed(p->ev[5], p->ev[6]) : 0.0;
+    p->timing.iterate_ms = timed && r.lag ? elapsed(p->ev[5], p->ev[6]) : iterate_ms;
     p->timing.sweep_ms = clock.ms;
     p->timing.sweeps_timed = (int32_t)clock.read;
     p->timing.iterations = hs->worked;

@@ -28,3 +28,23 @@ with api.Context(0) as ctx:
     assert failing_malloc.events() - before <= 128
     plan.close()
 """)
+
+
+def test_iterate_time_leaves_out_the_round_trips():
+    """With a step kernel per sweep the host reads the state between chunks of
+    launches: that time is in pagerank_ms and not in iterate_ms."""
+    import torch
+    from paper_2210_01465_amd import api, synth
+    s = synth.tiny(3)
+    with api.Context(0) as ctx:
+        plan = api.plan_create(ctx, s.radix, torch.from_numpy(s.fitness_raw).cuda())
+        kw = dict(tol=1e-30, max_iter=400, allow_noconv=True)   # never met: chunks of 8 to the cap
+        best = {}
+        for sep in (True, False):
+            for _ in range(3):
+                api.execute(plan, 0.85, separate_step=sep, **kw)
+                t = api.plan_timing(plan)
+                print(sep, t, flush=True)
+                best[sep] = min(best.get(sep, 1.0), t["iterate_ms"] / t["pagerank_ms"])
+        assert 0.0 < best[True] < 0.95 and 0.0 < best[False] <= 1.0
+        plan.close()
