@@ -1546,7 +1546,11 @@ fl_status execute_impl(fl_ctx *ctx, fl_plan *p, const fl_params *prm, double *d_
     } else {
         st = run_separate(ctx, p, r, a, lanes, grid, exact, clock, timed ? &iterate_ms : nullptr, &launches);
     }
-    if (st != FL_OK) return st;
+    if (st != FL_OK) {
+        // sweeps may still be under way: they would report to the next call
+        (void)hipStreamSynchronize(s);
+        return st;
+    }
     if (timed) FL_HIP(hipEventRecord(p->ev[3], s));
     FL_HIP(fl::launch_pr_output(a, d_pagerank, p->minima, (int32_t)p->m, d_minima, d_valid_raw, s));
     const double threshold = (1.0 + r.p) * (double)p->f_opt;

@@ -48,3 +48,36 @@ def test_iterate_time_leaves_out_the_round_trips():
                 best[sep] = min(best.get(sep, 1.0), t["iterate_ms"] / t["pagerank_ms"])
         assert 0.0 < best[True] < 0.95 and 0.0 < best[False] <= 1.0
         plan.close()
+
+
+def test_a_failed_call_leaves_no_sweeps_behind():
+    """A call that fails among its sweeps leaves none that could report a stop
+    to the next one (here: an event that cannot be created)."""
+    failing_malloc.run(r"""
+import numpy as np, torch
+from paper_2210_01465_amd import _abi, api
+radix = (12, 10, 6, 5, 4, 4, 3, 3, 3, 3)   # sweeps long enough to be under way for a while
+f = torch.from_numpy(np.random.default_rng(3).lognormal(0.0, 0.5, int(np.prod(radix))).astype(np.float32)).cuda()
+with api.Context(0) as ctx:
+    plan = api.plan_create(ctx, radix, f)
+    want, _, info = api.execute(plan, 0.85)
+    plan.close()
+last = 0
+for launch in range(info["iterations"] - 1, info["iterations"] + 5):   # one that follows the last sweep closely
+    with api.Context(0) as ctx:
+        plan = api.plan_create(ctx, radix, f)
+        got = torch.empty_like(want)
+        api.profile(ctx, 1)
+        failing_malloc.fail_event(2 * launch)
+        try:
+            api.execute(plan, 0.85)
+        except api.FLError as e:
+            assert e.status == _abi.FL_EHIP
+            last = launch
+        now = api.execute(plan, 0.85, pagerank=got)[2]
+        assert now["iterations"] == info["iterations"] and torch.equal(got, want), (launch, info, now)
+        failing_malloc.fail_event(-1)
+        plan.close()
+print(info["iterations"], "iterations; last refused at launch", last)
+assert last >= info["iterations"]
+""")
