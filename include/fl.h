@@ -21,6 +21,10 @@
  *   - All device work is ordered on the context's stream.  Input buffers are
  *     borrowed for the duration of the call; output buffers are owned by the
  *     caller.  Calls that return sizes or scores synchronise that stream.
+ *     While they wait for the device they poll pinned memory and keep a host
+ *     core busy; with hipDeviceScheduleBlockingSync or hipDeviceScheduleYield
+ *     set for the device they wait in the runtime instead, with longer gaps
+ *     between stages.
  *   - A context is not thread-safe: serialise calls that share one.
  *   - Configurations are numbered in mixed radix with parameter 0 the most
  *     significant digit: raw index I(x) = sum_i x_i * prod_{j>i} radix_j,

@@ -549,9 +549,24 @@ fl::HostSizes next_stamp(fl_ctx *ctx, const Build &b) {
     return {b.h_sizes, ++ctx->stamp};
 }
 
+// Whether the caller wants waits for this device to leave the core to others
+// instead of to spin.
+bool waits_block() {
+    unsigned flags = 0;
+    if (hipGetDeviceFlags(&flags) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return (flags & (hipDeviceScheduleYield | hipDeviceScheduleBlockingSync)) != 0;
+}
+
 // Waits until the stage launched last has reported its sizes.
 void build_wait(fl_ctx *ctx, Build &b) {
     if (b.status != FL_OK) return;
+    if (waits_block()) {
+        const hipError_t e = hipStreamSynchronize(ctx->stream);
+        if (e != hipSuccess) return build_fail(b, FL_EHIP, "build stage: %s", hipGetErrorString(e));
+    }
     for (uint32_t spins = 1; __atomic_load_n(&b.h_sizes->stamp, __ATOMIC_ACQUIRE) != ctx->stamp; ++spins) {
         __builtin_ia32_pause();
         if (spins % 4096 != 0) continue;
@@ -1414,16 +1429,21 @@ void read_progress(const uint64_t *word, Progress &p) {
 // fewer ahead.  With the step one sweep late (and the
 // power iteration's residual another), the sweep after the cap's last
 // iteration does only that step and stops.
+// Where waits are to block, the host waits for the stream instead, with more
+// launches ahead each time.
 constexpr int kSweepLead = 6;      // launches ahead of the last report: a launch takes the host about 3 us,
                                    // the shortest sweep 3, a report 1 to 2
 constexpr int kLastLead = 2;       // near the end
+constexpr int kBlockedLead = 16, kMaxBlockedLead = 64;   // where waits block: at first, and at most
 fl_status run_lagged(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int lanes, int grid, bool exact,
                      SweepClock &clock, int *launches_out) {
     hipStream_t s = ctx->stream;
     const int64_t limit = (int64_t)r.max_iter + (exact ? 1 : 2);
     __atomic_store_n(ctx->h_progress, uint64_t(0), __ATOMIC_RELEASE);
     a.progress = ctx->h_progress;
-    int64_t launches = 0, ahead = kSweepLead;
+    const bool blocked = waits_block();
+    const int most = blocked ? (exact ? kMaxBlockedLead : kBlockedLead) : kSweepLead;
+    int64_t launches = 0, ahead = most;
     Progress seen, now;
     uint32_t idle = 0;
     for (;;) {
@@ -1431,7 +1451,7 @@ fl_status run_lagged(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int 
         if (room) {
             a.sweep = (int32_t)launches;
             // (a pair's last launch lies at least kPairs back, before the one last reported)
-            static_assert(SweepClock::kPairs > kSweepLead, "pairs of events");
+            static_assert(SweepClock::kPairs > kSweepLead && SweepClock::kPairs >= kMaxBlockedLead, "pairs of events");
             const bool timed_here = clock.sampled(launches);
             fl_status st = timed_here ? clock.begin(s) : FL_OK;
             if (st != FL_OK) return st;
@@ -1439,7 +1459,9 @@ fl_status run_lagged(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int 
             if (timed_here) st = clock.end(s);
             if (st != FL_OK) return st;
             ++launches;
+            if (blocked) continue;
         }
+        if (blocked) FL_HIP(hipStreamSynchronize(s));
         read_progress(ctx->h_progress, now);
         if (now.stopped) break;
         if (now.sweep > seen.sweep) {
@@ -1448,7 +1470,7 @@ fl_status run_lagged(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int 
             if (!exact && seen.sweep >= 2 && now.resid > r.tol && seen.resid > now.resid) {
                 const double rate = log(now.resid / seen.resid) / (now.sweep - seen.sweep);
                 const double more = ceil(log(r.tol / now.resid) / rate);
-                ahead = (int64_t)std::min<double>(std::max<double>(more + 1.0, kLastLead), kSweepLead);
+                ahead = (int64_t)std::min<double>(std::max<double>(more + 1.0, kLastLead), blocked ? kMaxBlockedLead : most);
             }
             seen = now;
             idle = 0;
