@@ -189,8 +189,10 @@ class GpuBackend:
     def plan_bytes(self, plan) -> int:
         s = plan.sizes
         n, n_raw, e = int(s["n_valid"]), int(s["n_raw"]), int(s["n_edges"])
-        # in-edge lists of a small slot space, made when it first runs alone
+        # in-edge lists of a small slot space, made when it first runs alone; a
+        # plan whose lists would take more than 64 MiB keeps to its records
         lists = (n + 63) // 64 * 256 * (int(s["n_slots"]) + 32) if s["mask_words"] and e <= 7 << 18 else 0
+        lists = min(lists, 64 << 20)
         return n_raw * 16 + n * (8 * max(int(s["mask_words"]), 1) + 28) + 4 * e + lists
 
     def member_bytes(self, plan) -> int:
