@@ -161,7 +161,7 @@ def write_traffic(root: str, kernel_part: str, copy_bytes: int, command: str, tr
     return rec
 
 
-LOOP_KERNELS = ("k_batch_sweep<", "k_batch_finish<false>")
+LOOP_KERNELS = ("k_batch_sweep(", "k_batch_finish<false>")
 
 
 def write_loop_traffic(root: str, copy_bytes: int, runs: int, command: str) -> dict:

@@ -311,21 +311,6 @@ int auto_lanes(int64_t n, int64_t e) {
 
 bool valid_lanes(int l) { return l == 1 || l == 2 || l == 4 || l == 8 || l == 16 || l == 32 || l == 64; }
 
-// q / d == (q * m) >> (32 + l) for every q < 2^31, with l = ceil(log2 d) and
-// m = ceil(2^(32+l) / d) < 2^34 (Granlund and Montgomery, "Division by
-// invariant integers using multiplication", 1994, Thm. 4.2).
-void set_magic(SpaceDesc &sp) {
-    for (int k = 0; k < sp.n; ++k) {
-        const uint64_t d = (uint64_t)sp.radix[k];
-        uint32_t l = 0;
-        while ((uint64_t(1) << l) < d) ++l;
-        const uint32_t sh = 32 + l;
-        const unsigned __int128 num = (unsigned __int128)1 << sh;
-        sp.magic[k] = (uint64_t)((num + d - 1) / d);
-        sp.shift[k] = sh;
-    }
-}
-
 // Candidate slots sorted by raw-index offset: Hamming gives parameter k the
 // deltas +-1 .. +-(radix_k - 1), adjacent +-1.  A node record holds the slot
 // bits plus 40 bits of out_deg and raw index, in at most fl::kMaxWords words.
@@ -598,7 +583,6 @@ void build_begin(fl_ctx *ctx, Build &b, const fl_space *space, const float *fit,
     }
     for (int i = sp.n - 1; i >= 0; --i) sp.stride[i] = (i == sp.n - 1) ? 1 : sp.stride[i + 1] * sp.radix[i + 1];
     sp.n_raw = (int32_t)n_raw;
-    set_magic(sp);
 
     fl_plan *p = b.storage;
     if (p) *p = fl_plan{};
@@ -872,7 +856,6 @@ fl_status ensure_binned(fl_ctx *ctx, fl_plan *p, bool panels, const fl_plan::Bin
 struct Resolved {
     double d, p, tol;
     int32_t max_iter;
-    int lanes;  // FL_ROWS_SLOTS or CSR lanes
     bool lag;   // lagged step (no FL_STEP_SEPARATE)
 };
 
@@ -896,7 +879,6 @@ fl_status resolve_params(fl_ctx *ctx, const fl_plan *p, const fl_params *prm, Re
     r.tol = prm->tol_l1 > 0.0 ? prm->tol_l1 : 2e-7;
     // the exact sweeps settle after (longest path + 1) <= N sweeps
     r.max_iter = prm->max_iter > 0 ? prm->max_iter : (exact ? (int32_t)std::min<int64_t>(p->n + 2, INT32_MAX) : 1000);
-    r.lanes = prm->row_mapping ? prm->row_mapping : (p->sl.words > 0 ? FL_ROWS_SLOTS : FL_ROWS_BINNED);
     r.lag = !(prm->flags & FL_STEP_SEPARATE);
     return FL_OK;
 }

@@ -35,24 +35,24 @@ constexpr int kListQuads = 4;                     // quads of a wave's in-edge l
 constexpr int kLoneWaves = 2048;
 // Slot spaces of at most this many edges are swept by in-edge lists.  Per
 // sweep, lists against slots: 18 k nodes, 44 k edges 3.9 : 5.1 us; 124 k, 1.2 M
-// 6.8 : 7.4; 373 k, 1.5 M 8.7 : 8.6; 215 k, 3.7 M 14.3 : 9.6; 886 k, 15 M
-// 38.6 : 19.7.
+// 6.8 : 7.4; 215 k, 3.7 M 14.3 : 9.6; 886 k, 15 M 38.6 : 19.7.  Of 63 spaces of
+// 0.2 to 1.8 M edges that the rule takes, lists are 0.93 to 2.1 times as fast;
+// they lose where nodes are many and edges few (adjacent neighbours: 302 k
+// nodes, 1.5 M edges 8.4 : 7.9 us).  From there to 3.2 M edges adjacent spaces
+// lose up to a third (653 k, 3.1 M 15.3 : 10.0), Hamming spaces run from 0.89
+// (111 k, 2.4 M 8.4 : 7.5) to 1.7 (228 k, 2.2 M 9.6 : 16.0).
 constexpr int64_t kListEdges = 7 << 18;
 constexpr int kPanelBlock = 512;                  // threads of a workgroup of the lagged binned sweep (8 waves)
 constexpr int kFillStage = 6144;                  // col_idx entries of a tile assembled in LDS by the fill
 constexpr int kSmallTiles = 16;                   // batch members of at most this many tiles iterate in one workgroup
 
 // Mixed-radix description of a search space X = S_1 x ... x S_n, parameter 0
-// most significant: stride[i] = prod_{j>i} radix[j].  Digits are peeled off
-// from the least significant end with q / radix = (q * magic) >> shift, exact
-// for every q < 2^31 (Granlund-Montgomery with a 33-bit multiplier).
+// most significant: stride[i] = prod_{j>i} radix[j].
 struct SpaceDesc {
     int32_t n;
     int32_t n_raw;
     int32_t radix[kMaxParams];
     int32_t stride[kMaxParams];
-    uint64_t magic[kMaxParams];
-    uint32_t shift[kMaxParams];
 };
 
 // Candidate neighbour slots, numbered independently of the node: slot s moves

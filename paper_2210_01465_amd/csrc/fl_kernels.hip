@@ -1342,14 +1342,14 @@ __device__ __forceinline__ void tell_host(const PrArgs &a, int32_t stop, double 
     __hip_atomic_store(a.progress, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Workgroup 0 of sweep j >= 1: reduce the partial triples of sweep j - 1
-// in a fixed order (thread t sums parts t, t + B, ...; then a fixed
-// tree) and do its step.  Sweep j - 1 wrote sum w_j, the residual
-// |r_{j-1} - r_{j-2}| (zero for j = 1) and the sink part of sum w_j; for
-// the exact method, sum y_j, |y_j - y_{j-1}| and the sink part.
 // The initial iterate 1/N, rounded to FP32.
 __device__ __forceinline__ double lag_y0(int32_t n) { return (double)(float)(1.0 / (double)n); }
 
+// The first workgroup of sweep j >= 1: reduce the partial triples of sweep
+// j - 1 in a fixed order (thread t sums parts t, t + B, ...; then a fixed
+// tree) and do its step.  Sweep j - 1 wrote sum w_j, the residual
+// |r_{j-1} - r_{j-2}| (zero for j = 1) and the sink part of sum w_j; for
+// the exact method, sum y_j, |y_j - y_{j-1}| and the sink part.
 template <int B = kBlock>
 __device__ void lag_step(const PrArgs &a) {
     const int32_t j = a.sweep;
@@ -1932,6 +1932,7 @@ __device__ __forceinline__ void panel_sums_long(PanelRows &p, const int32_t *__r
     }
 }
 
+// Rows of fewer lanes, 64 / L of them at once per wave.
 template <int L>
 __device__ __forceinline__ void panel_sums(PanelRows &p, const int32_t *__restrict__ col_idx,
                                            const float *__restrict__ x, int32_t count) {
@@ -1940,12 +1941,7 @@ __device__ __forceinline__ void panel_sums(PanelRows &p, const int32_t *__restri
     for (int32_t r0 = (threadIdx.x >> 6) * kRowsPerStep; r0 < count; r0 += kWaves * kRowsPerStep) {
         const int32_t r = r0 + (int32_t)(threadIdx.x & 63) / L;
         const bool live = r < count;
-        int32_t b = live ? p.begin[r] : 0, e = live ? p.end[r] : 0;
-        if (L == 64) {
-            b = __builtin_amdgcn_readfirstlane(b);
-            e = __builtin_amdgcn_readfirstlane(e);
-        }
-        const float acc = row_gather<L>(col_idx, x, b, e, lane);
+        const float acc = row_gather<L>(col_idx, x, live ? p.begin[r] : 0, live ? p.end[r] : 0, lane);
         if (lane == 0 && live) p.acc[r] = acc;
     }
 }
@@ -2454,13 +2450,11 @@ __global__ __launch_bounds__(B) void k_pr_iter_lists(PrArgs a) {
 // the scalar unit and writes its own three FP64 partial sums, so a member's
 // result does not depend on which other members share the launch.  A member
 // whose stop flag is set is skipped.
-
 //
 // The list is grouped by record width (one launch for all of them: the widths
 // apart drained and filled the chip once each per sweep, 36 + 7 us against
 // 39 at 78 spaces).  XCD j takes the j-th eighth of every group, so that the
 // dearer tiles of the wide groups are spread over all of them.
-template <bool BUF>
 __global__ __launch_bounds__(kBlock) void k_batch_sweep(const BatchMember *__restrict__ members,
                                                         const TileRef *__restrict__ tiles,
                                                         const int32_t *__restrict__ ranges_dev) {
@@ -2505,11 +2499,11 @@ __global__ __launch_bounds__(kBlock) void k_batch_sweep(const BatchMember *__res
         q.k_pad = m->k_pad;
         q.x_bytes = m->x_bytes;
         switch (group) {
-            case 1: sweep_tile<1, BUF>(q, tile); break;
-            case 2: sweep_tile<2, BUF>(q, tile); break;
-            case 3: sweep_tile<3, BUF>(q, tile); break;
-            case 4: sweep_tile<4, BUF>(q, tile); break;
-            default: sweep_tile<5, BUF>(q, tile); break;
+            case 1: sweep_tile<1, true>(q, tile); break;
+            case 2: sweep_tile<2, true>(q, tile); break;
+            case 3: sweep_tile<3, true>(q, tile); break;
+            case 4: sweep_tile<4, true>(q, tile); break;
+            default: sweep_tile<5, true>(q, tile); break;
         }
     }
 }
@@ -3213,12 +3207,12 @@ hipError_t batch_sweep_binned_blocks_per_cu(int *blocks) {
 }
 
 hipError_t batch_sweep_blocks_per_cu(int *blocks) {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, (const void *)k_batch_sweep<true>, kBlock, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, (const void *)k_batch_sweep, kBlock, 0);
 }
 
 hipError_t launch_batch_sweep(const BatchMember *members, const TileRef *tiles, const int32_t *range_dev, int grid,
                               hipStream_t stream) {
-    hipLaunchKernelGGL(k_batch_sweep<true>, dim3(grid), dim3(kBlock), 0, stream, members, tiles, range_dev);
+    hipLaunchKernelGGL(k_batch_sweep, dim3(grid), dim3(kBlock), 0, stream, members, tiles, range_dev);
     return hipGetLastError();
 }
 
