@@ -30,7 +30,8 @@ arrive over time.  The server
 * keeps Python's cyclic garbage collector from running inside the loop (a
   full collection over the live request and tensor objects stalls the loop
   for tens of milliseconds): automatic collection is paused while ``run``
-  serves and the young generations are collected when the loop idles.
+  serves and the young generations are collected when the loop idles for
+  long enough.
 
 The GPU work goes through a backend object (``build``, ``plan_bytes``,
 ``member_bytes``, ``add``, ``step``, ``collect``, ``release``, plus ``plain``
@@ -50,6 +51,15 @@ import threading
 import time
 from dataclasses import dataclass, field
 from typing import Any, Callable, Hashable
+
+
+# Time a collection of the young generations takes per object in them, rounded
+# up (0.10 us at 2 700 objects, 0.20 us at 268 000, the 30 000 results of a busy
+# spell).  A server that falls idle between two requests collects only if that
+# ends before the next one: otherwise a spell without idle moments is followed
+# by a collection of tens of milliseconds in its first gap, with the requests
+# of that time waiting.
+_GC_SECONDS = 3e-7
 
 
 @dataclass(order=True)
@@ -492,7 +502,7 @@ class Server:
             elif pending and not self.queue:
                 wait = pending[0].arrival - (self.clock() - t0)
                 if wait > 0:
-                    if self.pause_gc:
+                    if self.pause_gc and gc.get_count()[0] * _GC_SECONDS < wait:
                         gc.collect(1)         # idle: young generations only
                         self.stats["gc_idle"] += 1
                         wait = pending[0].arrival - (self.clock() - t0)
