@@ -726,7 +726,7 @@ def main():
     ap.add_argument("--sweep-event-every", type=int, default=0, metavar="N",
                     help="bracket every N-th sweep launch of the timed steps with its own HIP events and "
                          "take the roofline's launch time from those (0, the default: from the events "
-                         "around each chunk of back-to-back sweep launches)")
+                         "around an analysis's back-to-back sweep launches)")
     args = ap.parse_args()
 
     if args.traffic_from:
@@ -818,7 +818,7 @@ def main():
     if args.sweep_event_every > 0:  # sweep kernels that did work, each between its own events
         avg_launch_s = sum(t["sweep_ms"] for t in timings) / 1e3 / sum(t["sweeps_timed"] for t in timings)
     else:
-        # events around each chunk of back-to-back sweep launches (the lagged
+        # events around an analysis's back-to-back sweep launches (the lagged
         # step launches no other kernel between them), over the sweeps that
         # did work: iterations + 2 per analysis (the step, and with it the
         # stop test, runs one sweep late, and one more sweep sees the stop)
@@ -836,7 +836,7 @@ def main():
     else:                           # CSR sweep reads the SpMV bytes, and 8 N more for the lagged step
         layout_bytes = bytes_per_launch + 8 * N
         layout_formula = "28 N + 8 E"
-        kernel = ("k_pr_iter_panels" if info["row_mapping"] == -2
+        kernel = ("k_pr_iter_panels or k_pr_iter_binned<true>" if info["row_mapping"] == -2
                   else f"k_pr_iter_csr<{info['row_mapping']}, true>")
     achieved = bytes_per_launch / avg_launch_s / 1e9
     traffic_rec = traffic_record(TRAFFIC_FILE, kernel)
@@ -880,8 +880,8 @@ def main():
                          "achieved_trace": traffic_rec.get("dram_gb_per_s"),
                          "frac_trace": (round(traffic_rec["dram_gb_per_s"] / HBM_PEAK_GBS, 4)
                                         if traffic_rec.get("dram_gb_per_s") else None)},
-                     "timing": ("HIP events on the engine's stream around each chunk of back-to-back sweep "
-                                "launches of the timed steps, over the sweeps that did work "
+                     "timing": ("HIP events on the engine's stream around the back-to-back sweep launches of "
+                                "each timed step, over the sweeps that did work "
                                 f"({sum(i['iterations'] + 2 for i in infos)})")
                                if args.sweep_event_every <= 0
                                else f"HIP events around every {args.sweep_event_every}th sweep launch "
