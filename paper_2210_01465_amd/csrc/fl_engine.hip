@@ -545,6 +545,11 @@ bool waits_block() {
     return (flags & (hipDeviceScheduleYield | hipDeviceScheduleBlockingSync)) != 0;
 }
 
+// Polls of pinned memory (of 30 to 60 ns) before a wait gives up polling and
+// waits for the stream, so that it ends whatever the runtime has put off: some
+// 10 ms, longer than any stage or sweep but those of the largest spaces.
+constexpr uint32_t kSpinLimit = 1u << 18;
+
 // Waits until the stage launched last has reported its sizes.
 void build_wait(fl_ctx *ctx, Build &b) {
     if (b.status != FL_OK) return;
@@ -555,7 +560,7 @@ void build_wait(fl_ctx *ctx, Build &b) {
     for (uint32_t spins = 1; __atomic_load_n(&b.h_sizes->stamp, __ATOMIC_ACQUIRE) != ctx->stamp; ++spins) {
         __builtin_ia32_pause();
         if (spins % 4096 != 0) continue;
-        const hipError_t q = hipStreamQuery(ctx->stream);
+        const hipError_t q = spins < kSpinLimit ? hipStreamQuery(ctx->stream) : hipStreamSynchronize(ctx->stream);
         if (q == hipErrorNotReady) {
             (void)hipGetLastError();
             continue;
@@ -1458,11 +1463,11 @@ fl_status run_lagged(fl_ctx *ctx, fl_plan *p, const Resolved &r, PrArgs &a, int 
             idle = 0;
         } else if (++idle % 4096 == 0) {
             // nothing new for a while: an error, or the stream has drained
-            const hipError_t q = hipStreamQuery(s);
+            const hipError_t q = idle < kSpinLimit ? hipStreamQuery(s) : hipStreamSynchronize(s);
             if (q == hipErrorNotReady) (void)hipGetLastError();
             if (q != hipSuccess && q != hipErrorNotReady) FL_HIP(q);
             read_progress(ctx->h_progress, now);
-            if (q == hipSuccess && launches >= limit && !now.stopped)
+            if (q == hipSuccess && !room && !now.stopped && now.sweep <= seen.sweep)
                 return fail(ctx, FL_EHIP, "the iteration did not stop after %lld sweeps", (long long)launches);
         } else if (!room) {
             __builtin_ia32_pause();
